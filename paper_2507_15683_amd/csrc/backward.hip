@@ -398,6 +398,7 @@ __device__ __forceinline__ void blend_bwd_item(const BackArgs& a, const int item
         s_g[slot][q] = 0.f;
       }
     }
+    __syncthreads();  // the next batch's staging overwrites s_rec
   }
 }
 

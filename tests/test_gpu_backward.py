@@ -457,3 +457,33 @@ def test_backward_schedules_agree(hg, tile):
         for k in ("pose", "means"):
             assert _rel(r1[k], r0[k]) < 1e-5, (sched, "residual", k)
         assert np.array_equal(l1, l0), (sched, "loss")
+
+
+@pytest.mark.parametrize("D,tile", [(0, 8), (8, 16), (16, 32), (32, 16), (32, 8), (64, 16)])
+def test_long_lists_give_every_record_its_own_sums(hg, D, tile):
+    """Tile lists of several staging rounds (hundreds of entries): the
+    gradients of two runs, and of two tile sizes, agree to float-atomic and
+    summation-order rounding (1e-5 of the norm), so no round's sums reach the
+    records of the next one."""
+    import torch
+    sc, P, cam = synth.tiny_scene(4000, 95 + D, width=83, height=61, feat_dim=D, sh_degree=3)
+    sc = sc.copy()
+    sc.opacities[:] *= 0.15  # long walks: many splats blend before a pixel stops
+    Ps = synth.perturb_poses(P[0], 4, 96, 1.0, 2.0)
+    scene = hg.GaussianScene.from_numpy(sc)
+    K = hg.Intrinsics.of(cam)
+    log(f"case: long lists D={D} tile={tile}")
+    gen = torch.Generator(device="cuda").manual_seed(97)
+    want = ("pose", "means", "opacities", "log_scales", "quats", "sh") + (("feat",) if D else ())
+    r = hg.Renderer()
+    ref = None
+    for t in (tile, tile, 8 if tile != 8 else 16):
+        out = r.render(scene, _t(Ps), K, tile=t)
+        if ref is None:
+            assert r.stats()["max_tile_list"] > 150  # several rounds of 64 or 128
+            go = {k: torch.randn(v.shape, generator=gen, device="cuda") for k, v in out.items() if v is not None}
+        g = {k: to_np(v).copy() for k, v in r.backward(go, want=want).items()}
+        if ref is None:
+            ref = g
+        for k in want:
+            assert _rel(g[k], ref[k]) < 1e-5, (k, t)
