@@ -7,8 +7,8 @@
 // S_j = sum_{k>j} w_k h_k,
 //   dL/dalpha_j = T_j h_j - (S_j + gT T_final) / (1 - alpha_j),
 // where gT collects the outputs' direct dependence on T_final (background,
-// depth normalisation, alpha).  Per-splat gradients are summed across the
-// 64 lanes of a wave before one atomic per value.
+// depth normalisation, alpha).  Per-splat sums are formed per wave, then per
+// workgroup, before one atomic per value.
 //
 // project_bwd: one thread per visible (pose, Gaussian): chains the splat
 // gradients through the conic inverse, the EWA covariance, the clamped
@@ -20,162 +20,487 @@
 
 namespace hgsr {
 
-typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef short shortx4 __attribute__((ext_vector_type(4)));
 
-// Splats per matrix-core group of the feature term (MFH).
-constexpr int kHGroup = 32;
+// The blend backward's work split, at every tile size: a wave owns an 8x8
+// block of pixels, one per lane, and a workgroup owns a 16x16 block (tile 8:
+// 8x8).  A 32x32 tile is four workgroups that walk the same list, each over
+// one quadrant.
+template <int TILE>
+struct BwdShape {
+  static constexpr int kThreads = TILE == 8 ? 64 : 256;
+  static constexpr int kWaves = kThreads / kWave;
+  static constexpr int kParts = TILE == 32 ? 4 : 1;  // workgroups per tile
+};
+constexpr int kBwdBatch = 64;   // splats staged per round: a wave's hits are one 64-bit mask
+constexpr int kBwdGroup = 16;   // splats per matrix-core product
+constexpr int kBwdHalf = 8;     // splats per transposed reduction
+constexpr int kBwdRow = 68;     // words per LDS row of 64 pixels (16-byte reads of 8 rows hit 32 banks)
+constexpr int kBwdGcRow = 8;    // words per row of 8 pixel gradients
 
-// MFH: the feature part of h_j = gF . f_j for a group of 32 splats and the
-// wave's 64 pixels is one matrix product H[32 x 64] = F[32 x 32] gF[32 x 64],
-// run as v_mfma_f32_32x32x8_bf16 (channels in four steps of 8, pixels in two
-// blocks of 32).  F is the splats' stored bf16 features (exact); the FP32
-// pixel gradient gF enters as three bf16 parts (top, middle and last 8
-// significant bits), so the products are exact and only the summation order
-// differs from the FP32 dot product.  H goes to LDS, where the walk reads its
-// pixel's value of each splat.
-// PO (pose only, residual loss): the opacity and depth sums are not formed
-// (the residual has no depth term and no opacity gradient was asked for),
-// eight sums per splat instead of ten.
-template <int TILE, int D, bool FEATGRAD, bool RES, bool MFH, bool PO>
+// Item order of a grid launch whose poses share one target: a run's target
+// block (16 tiles: 0.6 MB at 32 channels) is then fetched once per block of
+// poses into the XCD's L2, whose poses still pass over neighbouring tiles
+// close together (records and half lines of the maps).  64 poses at 960x540:
+// 3,323 -> 3,258 us, 16 at 480x270: 266 -> 251 us; all poses per run 3-5 %
+// slower than pose after pose, runs of 60 tiles no faster.
+constexpr int kPoseBlock = 8;
+constexpr int kTileRun = 16;
+
+// Transpose of a 4x4 block whose one index is the register and whose other is
+// the row of 16 lanes: afterwards register k of lane row m holds what register
+// m of lane row k held.
+__device__ __forceinline__ void transpose_rows(uint32_t& r0, uint32_t& r1, uint32_t& r2, uint32_t& r3) {
+  const auto a = __builtin_amdgcn_permlane32_swap(r0, r2, false, false);
+  const auto b = __builtin_amdgcn_permlane32_swap(r1, r3, false, false);
+  const auto c = __builtin_amdgcn_permlane16_swap(a[0], b[0], false, false);
+  const auto d = __builtin_amdgcn_permlane16_swap(a[1], b[1], false, false);
+  r0 = c[0];
+  r1 = c[1];
+  r2 = d[0];
+  r3 = d[1];
+}
+
+// Sum over the four rows of 16 lanes, in every lane.
+__device__ __forceinline__ float row_quad_sum(float v) {
+  const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  const float t = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+  const auto b = __builtin_amdgcn_permlane16_swap(__float_as_uint(t), __float_as_uint(t), false, false);
+  return __uint_as_float(b[0]) + __uint_as_float(b[1]);
+}
+
+// v of each row of 16 lanes, in every row.
+__device__ __forceinline__ void row_broadcast(float v, float out[4]) {
+  const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  const auto a = __builtin_amdgcn_permlane16_swap(h[0], h[0], false, false);
+  const auto b = __builtin_amdgcn_permlane16_swap(h[1], h[1], false, false);
+  out[0] = __uint_as_float(a[0]);
+  out[1] = __uint_as_float(a[1]);
+  out[2] = __uint_as_float(b[0]);
+  out[3] = __uint_as_float(b[1]);
+}
+
+// Orders this wave's LDS writes before its LDS reads (and the reverse).
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Sums eight per-lane values over the eight lane octets (lanes that agree in
+// lane % 8): on return the lane holds the total of value lane / 8.
+__device__ __forceinline__ float octet_scatter8(const float v[8], int lane) {
+  float b[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[i]), __float_as_uint(v[4 + i]), false, false);
+    b[i] = __uint_as_float(s[0]) + __uint_as_float(s[1]);
+  }
+  const auto s0 = __builtin_amdgcn_permlane16_swap(__float_as_uint(b[0]), __float_as_uint(b[2]), false, false);
+  const auto s1 = __builtin_amdgcn_permlane16_swap(__float_as_uint(b[1]), __float_as_uint(b[3]), false, false);
+  const float c0 = __uint_as_float(s0[0]) + __uint_as_float(s0[1]);
+  const float c1 = __uint_as_float(s1[0]) + __uint_as_float(s1[1]);
+  const bool odd = (lane & 8) != 0;
+  return (odd ? c1 : c0) + row_ror<8>(odd ? c0 : c1);
+}
+
+// The same for two values: lanes 0-7 end with the total of a, lanes 32-39 with
+// that of b.
+__device__ __forceinline__ float octet_sum2(float a, float b) {
+  const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  const float t = __uint_as_float(s[0]) + __uint_as_float(s[1]);
+  const auto u = __builtin_amdgcn_permlane16_swap(__float_as_uint(t), __float_as_uint(t), false, false);
+  const float w = __uint_as_float(u[0]) + __uint_as_float(u[1]);
+  return w + row_ror<8>(w);
+}
+
+// Element of a plane at a byte offset.
+template <class E>
+__device__ __forceinline__ E plane_at(const E* base, uint32_t bytes) {
+  return *reinterpret_cast<const E*>(reinterpret_cast<const char*>(base) + bytes);
+}
+
+__device__ __forceinline__ bool finite_bits(float v) { return (__float_as_uint(v) & 0x7f800000u) != 0x7f800000u; }
+
+// The reverse replay of one (pose, tile) or tile quadrant.
+//
+// Bound by the VALU (about 2,500 instructions per wave of 35 splats, 70 % busy)
+// beside the feature maps' traffic.  A splat's gradient sums over a wave's 64
+// pixels are not reduced across lanes splat by splat: each lane writes two
+// numbers per splat to LDS, dL/dpower d and the blend weight w, and after eight
+// splats the wave reads them back transposed -- a lane takes one splat's row of
+// eight pixels -- and forms the sums of d, d dx, d dx^2 and w g there, every
+// lane busy, with one cross-lane step per eight splats.  The sums kept per
+// record are the moments (sum d dx, d dy, d dx^2, d dx dy, d dy^2, d, w gZ,
+// w gC); the projection backward turns them into conic, mean and opacity
+// gradients.  The waves keep their sums apart in LDS until the flush: float
+// atomics there take about a cycle per lane (300 of 3,700 us at 64 poses).
+//
+// The feature part of h_j = gF . f_j is, for 16 splats and 64 pixels, a matrix
+// product on the matrix cores (v_mfma_f32_16x16x32_bf16; 16x16x16 for up to 16
+// channels): the splats' stored bf16 features enter exactly, the FP32 pixel
+// gradient in three exact bf16 parts kept in registers for the whole tile, so
+// products are exact and only the order of the sum differs from the FP32 dot
+// product.  The FP32 matrix form (16x16x4, no split) took 400 us more at 64
+// poses.  The pixel gradients are loaded in the operand's own layout, every
+// load issued before the first wait (flags, tile range and list follow), and a
+// splat's geometry and colour are read from LDS a step ahead.
+//
+// FEATGRAD: a splat's feature gradient sum_p w_p gF_p is the product of the
+// weights (16 splats x 64 pixels, read transposed from LDS) with the FP32 pixel
+// gradients in registers, in FP32 on the matrix cores
+// (v_mfma_f32_16x16x4_f32), summed per workgroup in LDS before the global
+// atomics; the form it replaces summed every channel over the wave by shuffles
+// and added it to memory from one lane.
+//
+// Before and after, blend backward alone: 64 poses at 960x540, 32 channels,
+// pose only: 3,744 -> 3,260 us; 16 poses at 480x270: 291 -> 251 us; one pose
+// at 480x270: 98 -> 63 us; one 640x480 view with all Gaussian gradients: 711 ->
+// 133 us.  Five waves per SIMD (96 registers) spill: 5,040 us at 64 poses.
+//
+// Non-finite output gradients reach only the splats blended at their pixels:
+// a wave that holds any (`bad`) leaves zero weights out of its sums.
+//
+// PO (pose only, residual loss): neither the opacity nor the depth sum is
+// formed (the residual has no depth term and no opacity gradient was asked
+// for).
+template <int TILE, int D, bool FEATGRAD, bool RES, bool PO>
 __device__ __forceinline__ void blend_bwd_item(const BackArgs& a, const int item) {
-  using Sh = BlendShape<TILE>;
-  constexpr int NT = Sh::kThreads, NB = Sh::kBatch, NW = Sh::kWaves, BW = Sh::kBlockW, BH = Sh::kBlockH;
-  constexpr int PPT = Sh::kPPT;
-  constexpr int DV = D / 8;                             // 16-byte bf16 vectors per feature
-  constexpr int DD = D > 0 ? D : 1;
-  constexpr int PARTS = (DV >= NT / NB) ? NT / NB : 1;  // threads sharing one splat's feature load
-  constexpr bool MF = MFH && D == 32 && PPT == 1 && !FEATGRAD;
-  __shared__ float4 s_geo[NB];
-  __shared__ float4 s_opz[NB];
-  __shared__ float4 s_col[NB];
-  __shared__ uint32_t s_rec[NB];
-  constexpr int FS = D + 4;  // padded slot stride (words): staging writes spread over banks
-  __shared__ float s_f[(D > 0 && !MF) ? NB * FS : 1];  // features as FP32
-  constexpr int FBS = 20;    // MF: raw bf16 feature slot (16 words + 4 of padding)
-  __shared__ uint32_t s_fb[MF ? NB * FBS : 1];
-  __shared__ float s_h[MF ? NW : 1][MF ? kHGroup : 1][MF ? kWave : 1];  // MF: H per wave
-  __shared__ uint8_t s_mask[NB];
-  __shared__ uint16_t s_list[NW][NB];
-  __shared__ float s_g[NB][10];  // per staged splat: the workgroup's gradient sums
+  using Sh = BwdShape<TILE>;
+  constexpr int NT = Sh::kThreads, NW = Sh::kWaves, NB = kBwdBatch, ROW = kBwdRow;
+  constexpr int DV = D / 8;                    // 16-byte bf16 vectors per feature
+  constexpr int CG = D / 4;                    // channels per lane row of the matrix operands
+  constexpr int CGA = CG > 0 ? CG : 1;
+  constexpr int KW = CG > 4 ? 4 : 2;           // words per operand of one matrix step (16x16x32 or x16)
+  constexpr int KS = CG > 8 ? CG / 8 : 1;      // matrix steps
+  constexpr int NV = PO ? 8 : 10;              // moment sums per splat
+  constexpr int GR = NB + 1;                   // words per row of sums (one row per value)
+  constexpr int NBL = FEATGRAD ? (D + 15) / 16 : 1;    // FEATGRAD: blocks of 16 channels
+  constexpr int SHARE = NT / NB;               // threads staging one splat
+  constexpr int FBS = D > 0 ? D / 2 + 4 : 4;   // words per staged bf16 feature vector (padded)
+  constexpr int WR = FEATGRAD ? kBwdGroup : kBwdHalf;  // rows of weights kept
+  constexpr int GS = D + 1;                    // FEATGRAD: words per pixel's gradient and per splat's feature sum
+  struct Walk {
+    float4 sp[NB][4];                          // u v ca cb | cc o z gid | r g b pmin | record index
+    uint32_t fb[NB * FBS];                     // bf16 feature vectors
+    float d[NW][kBwdHalf][ROW];                // dL/dpower per splat (row) and pixel
+    float w[NW][WR][ROW];                      // blend weight
+    float gc[NW][PO ? 3 : 4][8 * kBwdGcRow];   // gC, gZ planes of each wave's 8x8 pixels
+    float g[NW][NV * GR];                      // per wave and staged splat: moment sums (where the wave hit it)
+    uint64_t hits[NW];                         // the waves' hits of the round
+    float gfe[FEATGRAD ? NB * GS : 1];         // FEATGRAD: and its feature sums
+    uint8_t mask[NB];
+    uint8_t list[NW][NB];                      // slots of each wave's hits, back to front
+  };
+  union Lds {
+    Walk walk;
+    float gf[FEATGRAD ? NW : 1][FEATGRAD ? kWave * GS : 1];  // FEATGRAD prologue: per pixel dL/d(feature map)
+  };
+  __shared__ __align__(16) Lds s_u;
   __shared__ uint32_t s_max;
   __shared__ float s_lw[NW];
+  auto& s_sp = s_u.walk.sp;
+  auto& s_fb = s_u.walk.fb;
+  auto& s_d = s_u.walk.d;
+  auto& s_w = s_u.walk.w;
+  auto& s_gc = s_u.walk.gc;
+  auto& s_g = s_u.walk.g;
+  auto& s_hits = s_u.walk.hits;
+  auto& s_gfe = s_u.walk.gfe;
+  auto& s_mask = s_u.walk.mask;
+  auto& s_list = s_u.walk.list;
   const int tid = threadIdx.x;
   const int lane = tid & (kWave - 1), wave = tid >> 6;
   const int W = a.c.W, H = a.c.H;
   const int64_t HW = static_cast<int64_t>(W) * H;
+  const int part = item % Sh::kParts, titem = item / Sh::kParts;
   int pose, tile;
   if (a.schedule == kSchedTileMajor) {
-    tile = item / a.P;
-    pose = item - tile * a.P;
+    tile = titem / a.P;
+    pose = titem - tile * a.P;
+  } else if (a.share_target) {
+    // blocks of kPoseBlock poses; within one, runs of kTileRun neighbouring
+    // tiles, each run for the block's poses in turn
+    const int tiles = a.c.tiles_per_pose;
+    const int block = titem / (kPoseBlock * tiles), r = titem - block * kPoseBlock * tiles;
+    const int np = min(kPoseBlock, a.P - block * kPoseBlock);
+    const int run = r / (kTileRun * np), r2 = r - run * kTileRun * np;
+    const int size = min(kTileRun, tiles - run * kTileRun);
+    const int pi = r2 / size;
+    pose = block * kPoseBlock + pi;
+    tile = run * kTileRun + (r2 - pi * size);
   } else {
-    pose = item / a.c.tiles_per_pose;
-    tile = item - pose * a.c.tiles_per_pose;
+    pose = titem / a.c.tiles_per_pose;
+    tile = titem - pose * a.c.tiles_per_pose;
   }
   const int ty = tile / a.c.ntx, tx = tile - ty * a.c.ntx;
-  const uint2 range = a.ranges[static_cast<int64_t>(pose) * a.c.tiles_per_pose + tile];
-  const int bx0 = tx * TILE + (wave % Sh::kBlocksX) * BW, by0 = ty * TILE + (wave / Sh::kBlocksX) * BH;
+  const int bx0 = tx * TILE + (part & 1) * 16 + (wave & 1) * 8, by0 = ty * TILE + (part >> 1) * 16 + (wave >> 1) * 8;
+  const int mask_bit = TILE == 32 ? part : wave;  // the list masks' block that holds this wave's pixels
 
-  float pxf[PPT], pyf[PPT], T[PPT], Tf[PPT], S[PPT], gC[PPT][3], GZ[PPT], gT[PPT];
-  float gF[PPT][DD];
-  uint32_t last[PPT];
+  // a round's staging: list entry, then record and feature vector, dealt to
+  // the splat's SHARE threads and held in registers until the LDS is free
+  constexpr int RV = (3 + SHARE - 1) / SHARE, FV = DV > 0 ? (DV + SHARE - 1) / SHARE : 1;
+  const int st_e = tid / SHARE, st_sub = tid % SHARE;
+  uint32_t st_lv = 0, st_gid = 0;
+  float4 st_rec[RV];
+  uint4 st_feat[FV];
+  auto stage_index = [&](uint2 range, uint32_t b0) {
+    const uint32_t j = range.x + b0 + st_e;
+    if (j < range.y) {
+      st_lv = a.list[j];
+      st_gid = a.list_gid[j];
+    }
+  };
+  auto stage_load = [&](uint2 range, uint32_t b0) {
+    if (range.x + b0 + st_e < range.y) {
+      const float4* sp = reinterpret_cast<const float4*>(a.recs + (st_lv & kRecMask));
+#pragma unroll
+      for (int q = 0; q < RV; ++q)
+        if (q * SHARE + st_sub < 3) st_rec[q] = sp[q * SHARE + st_sub];
+      if constexpr (DV > 0) {
+        const uint4* fv = reinterpret_cast<const uint4*>(a.feat) + static_cast<int64_t>(st_gid) * DV;
+#pragma unroll
+        for (int q = 0; q < FV; ++q)
+          if (q * SHARE + st_sub < DV) st_feat[q] = fv[q * SHARE + st_sub];
+      }
+    }
+  };
+  auto stage_store = [&](int nb) {
+    if (st_e < nb) {
+#pragma unroll
+      for (int q = 0; q < RV; ++q)
+        if (q * SHARE + st_sub < 3) s_sp[st_e][q * SHARE + st_sub] = st_rec[q];
+      if constexpr (DV > 0) {
+#pragma unroll
+        for (int q = 0; q < FV; ++q)
+          if (q * SHARE + st_sub < DV)
+            reinterpret_cast<uint4*>(&s_fb[st_e * FBS])[q * SHARE + st_sub] = st_feat[q];
+      }
+      if (st_sub == SHARE - 1) {
+        s_sp[st_e][3].x = __uint_as_float(st_lv & kRecMask);
+        s_mask[st_e] = static_cast<uint8_t>(st_lv >> kRecBits);  // blocks the support meets
+      }
+    }
+  };
   if (tid == 0) s_max = 0;
-  for (int e = tid; e < NB * 10; e += NT) (&s_g[0][0])[e] = 0.f;
-  __syncthreads();
-  uint32_t my_max = 0;
-  float lsum = 0.f;  // this lane's residual terms (RES)
-#pragma unroll
-  for (int k = 0; k < PPT; ++k) {
-    const int li = lane + k * kWave;
-    const int px = bx0 + (li % BW), py = by0 + (li / BW);
-    const bool inside = px < W && py < H;
-    pxf[k] = static_cast<float>(px) + 0.5f;
-    pyf[k] = static_cast<float>(py) + 0.5f;
-    last[k] = 0;
-    T[k] = Tf[k] = 1.f;
-    S[k] = 0.f;
-    gC[k][0] = gC[k][1] = gC[k][2] = 0.f;
-    GZ[k] = gT[k] = 0.f;
-#pragma unroll
-    for (int d = 0; d < DD; ++d) gF[k][d] = 0.f;
-    if (!inside) continue;
-    const int64_t pix = static_cast<int64_t>(py) * W + px;
-    const int64_t o = static_cast<int64_t>(pose) * HW + pix;
-    last[k] = a.n_used[o];
-    Tf[k] = T[k] = a.final_T[o];
-    const float A = 1.f - Tf[k];
-    float gtv = 0.f;
+  const int px = bx0 + (lane & 7), py = by0 + (lane >> 3);
+  const float pxf = static_cast<float>(px) + 0.5f, pyf = static_cast<float>(py) + 0.5f;
+  const int64_t po = static_cast<int64_t>(pose) * HW;
+  const int64_t tp = RES ? static_cast<int64_t>(pose) * a.res_t_stride : 0;
+  const bool inside = px < W && py < H;
+
+  // Every load that the list does not order goes out first: this pixel's saved
+  // state and colours, and the feature maps, so that one memory round trip
+  // covers them (the flags, the range and the list's first entries follow).
+  uint32_t last = 0;
+  float T = 1.f, Tf = 1.f, gC[3] = {0.f, 0.f, 0.f}, GZ = 0.f, gT = 0.f;
+  float cf[3] = {0.f, 0.f, 0.f}, ct[3] = {0.f, 0.f, 0.f};
+  // planes are read at a wave-uniform base plus one 32-bit byte offset (an
+  // image has at most 2^28 pixels)
+  const uint32_t pix = 4u * (static_cast<uint32_t>(min(py, H - 1)) * static_cast<uint32_t>(W) +
+                             static_cast<uint32_t>(min(px, W - 1)));
+  if (inside) {
+    last = plane_at(a.n_used + po, pix);
+    Tf = plane_at(a.final_T + po, pix);
     if constexpr (RES) {
-      // the residual's gradient at this pixel (the definition the residual
-      // kernel evaluates), from the forward's outputs and the target
-      const float inv = a.res_inv_hw;
-      const int64_t o3 = static_cast<int64_t>(pose) * 3 * HW + pix;
-      const int64_t tp = static_cast<int64_t>(pose) * a.res_t_stride;
-      float l = 0.f;
 #pragma unroll
       for (int ch = 0; ch < 3; ++ch) {
-        const float d = a.fwd_rgb[o3 + ch * HW] - a.res_rgb_t[tp * 3 * HW + pix + ch * HW];
-        l += fabsf(d);
-        gC[k][ch] = d > 0.f ? inv : (d < 0.f ? -inv : 0.f);
+        cf[ch] = plane_at(a.fwd_rgb + (3 * po + ch * HW), pix);
+        ct[ch] = plane_at(a.res_rgb_t + (3 * tp + ch) * HW, pix);
       }
-      gtv = gC[k][0] * a.bg[0] + gC[k][1] * a.bg[1] + gC[k][2] * a.bg[2];
-      if constexpr (D > 0) {
-        const int64_t of = static_cast<int64_t>(pose) * D * HW + pix;
-        const int64_t tf = tp * D * HW + pix;
-        float t[D];
-        float dot = 0.f, na = 0.f, nb = 0.f;
-#pragma unroll
-        for (int d = 0; d < D; ++d) {
-          gF[k][d] = a.fwd_feat_bf16 ? bf16_lo(static_cast<const uint16_t*>(a.fwd_feat)[of + d * HW])
-                                     : static_cast<const float*>(a.fwd_feat)[of + d * HW];
-          t[d] = a.res_feat_t[tf + d * HW];
-          dot = fmaf(gF[k][d], t[d], dot);
-          na = fmaf(gF[k][d], gF[k][d], na);
-          nb = fmaf(t[d], t[d], nb);
-        }
-        na = sqrtf(na);
-        nb = sqrtf(nb);
-        const float n = na * nb + kCosEps;
-        const float cosv = dot / n;
-        l += a.res_lam * (1.f - cosv);
-        const float s1 = -a.res_lam * inv / n;
-        const float s2 = na > 0.f ? a.res_lam * inv * dot * nb / (n * n * na) : 0.f;
-#pragma unroll
-        for (int d = 0; d < D; ++d) gF[k][d] = s1 * t[d] + s2 * gF[k][d];
-      }
-      lsum += l * inv;
     } else if (a.g_rgb) {
-      const int64_t o3 = static_cast<int64_t>(pose) * 3 * HW + pix;
-      gC[k][0] = a.g_rgb[o3];
-      gC[k][1] = a.g_rgb[o3 + HW];
-      gC[k][2] = a.g_rgb[o3 + 2 * HW];
-      gtv = gC[k][0] * a.bg[0] + gC[k][1] * a.bg[1] + gC[k][2] * a.bg[2];
-    }
-    if (a.g_depth && A > 0.f) {
-      const float gd = a.g_depth[o];
-      GZ[k] = gd / A;
-      gtv += gd * a.fwd_depth[o] / A;
-    }
-    if (a.g_alpha) gtv -= a.g_alpha[o];
-    gT[k] = gtv;
-    if constexpr (D > 0 && !RES) {
-      if (a.g_feat) {
-        const int64_t of = static_cast<int64_t>(pose) * D * HW + pix;
 #pragma unroll
-        for (int d = 0; d < D; ++d) gF[k][d] = a.g_feat[of + d * HW];
+      for (int ch = 0; ch < 3; ++ch) gC[ch] = plane_at(a.g_rgb + (3 * po + ch * HW), pix);
+    }
+  }
+  // B operands of the feature term, loaded in their own layout: lane l holds
+  // channels CG (l / 16) + s of pixel 16 b + l % 16 (a pixel outside the image
+  // reads the nearest one inside: it blends nothing)
+  float gb[CGA][4] = {};
+  float gt[RES ? CGA : 1][4];
+  bool have_gf = false;
+  if constexpr (D > 0) have_gf = RES || a.g_feat != nullptr;
+  if constexpr (D > 0) {
+    // per pixel block the lane's element of channel s: a uniform base (plane s)
+    // plus 32-bit element offsets, where the lane rows' planes lie within reach
+    uint32_t xy[4];
+    auto load_operands = [&](int64_t row) {
+      if constexpr (RES) {
+        const float* tb = a.res_feat_t + tp * D * HW + row;
+#pragma unroll
+        for (int s = 0; s < CG; ++s)
+#pragma unroll
+          for (int b = 0; b < 4; ++b) gt[s][b] = plane_at(tb + s * HW, xy[b]);
+        if (a.fwd_feat_bf16) {
+          const uint16_t* fb = static_cast<const uint16_t*>(a.fwd_feat) + D * po + row;
+#pragma unroll
+          for (int s = 0; s < CG; ++s)
+#pragma unroll
+            for (int b = 0; b < 4; ++b) gb[s][b] = bf16_lo(plane_at(fb + s * HW, xy[b] / 2));
+        } else {
+          const float* fb = static_cast<const float*>(a.fwd_feat) + D * po + row;
+#pragma unroll
+          for (int s = 0; s < CG; ++s)
+#pragma unroll
+            for (int b = 0; b < 4; ++b) gb[s][b] = plane_at(fb + s * HW, xy[b]);
+        }
+      } else if (have_gf) {
+        const float* gp = a.g_feat + D * po + row;
+#pragma unroll
+        for (int s = 0; s < CG; ++s)
+#pragma unroll
+          for (int b = 0; b < 4; ++b) gb[s][b] = plane_at(gp + s * HW, xy[b]);
+      }
+    };
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+      xy[b] = static_cast<uint32_t>(min(by0 + 2 * b + ((lane >> 3) & 1), H - 1)) * static_cast<uint32_t>(W) +
+              static_cast<uint32_t>(min(bx0 + (lane & 7), W - 1));
+    if (static_cast<int64_t>(D) * HW < (1ll << 30)) {
+      const uint32_t row = static_cast<uint32_t>(CG * (lane >> 4)) * static_cast<uint32_t>(HW);
+#pragma unroll
+      for (int b = 0; b < 4; ++b) xy[b] = (xy[b] + row) * 4u;
+      load_operands(0);
+    } else {
+#pragma unroll
+      for (int b = 0; b < 4; ++b) xy[b] *= 4u;
+      load_operands(CG * (lane >> 4) * HW);
+    }
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  if (a.flags[0] & 3) return;  // uniform: the render overflowed, its lists are not valid
+  const uint2 range = a.ranges[static_cast<int64_t>(pose) * a.c.tiles_per_pose + tile];
+  // the list's last round is the first one walked, unless every pixel stopped
+  // before it
+  uint32_t staged = range.y > range.x ? (range.y - range.x - 1) / NB * NB : 0u;
+  if (range.y > range.x) stage_index(range, staged);
+  __builtin_amdgcn_sched_barrier(0);
+
+  T = Tf;
+  float lsum = 0.f;  // this thread's residual terms (RES)
+  if (inside) {
+    const float A = 1.f - Tf;
+    if constexpr (RES) {
+      const float inv = a.res_inv_hw;
+#pragma unroll
+      for (int ch = 0; ch < 3; ++ch) {
+        const float d = cf[ch] - ct[ch];
+        lsum += fabsf(d);
+        gC[ch] = d > 0.f ? inv : (d < 0.f ? -inv : 0.f);
       }
     }
-    my_max = max(my_max, last[k]);
+    gT = gC[0] * a.bg[0] + gC[1] * a.bg[1] + gC[2] * a.bg[2];
+    if (a.g_depth && A > 0.f) {
+      const float gd = plane_at(a.g_depth + po, pix);
+      GZ = gd / A;
+      gT += gd * plane_at(a.fwd_depth + po, pix) / A;
+    }
+    if (a.g_alpha) gT -= plane_at(a.g_alpha + po, pix);
   }
-  // list positions this wave must visit: below the largest saved length
+  if constexpr (RES && D > 0) {
+    // the residual's gradient (the definition the residual kernel evaluates):
+    // sums over this lane's channels, then over the four lane rows; the lane
+    // row b then forms block b's factors for all four
+    float dot = 0.f, na = 0.f, nb = 0.f;
 #pragma unroll
-  for (int off = 32; off > 0; off >>= 1) my_max = max(my_max, static_cast<uint32_t>(__shfl_xor(my_max, off, kWave)));
-  const uint32_t wave_max = my_max;
+    for (int b = 0; b < 4; ++b) {
+      float d = 0.f, n = 0.f, m = 0.f;
+#pragma unroll
+      for (int s = 0; s < CG; ++s) {
+        d = fmaf(gb[s][b], gt[s][b], d);
+        n = fmaf(gb[s][b], gb[s][b], n);
+        m = fmaf(gt[s][b], gt[s][b], m);
+      }
+      d = row_quad_sum(d);
+      n = row_quad_sum(n);
+      m = row_quad_sum(m);
+      const bool mine = (lane >> 4) == b;
+      dot = mine ? d : dot;
+      na = mine ? n : na;
+      nb = mine ? m : nb;
+    }
+    na = sqrtf(na);
+    nb = sqrtf(nb);
+    const float n = na * nb + kCosEps;
+    const float inv = a.res_inv_hw;
+    if (inside) lsum += a.res_lam * (1.f - dot / n);
+    const float s1 = -a.res_lam * inv / n;
+    const float s2 = na > 0.f ? a.res_lam * inv * dot * nb / (n * n * na) : 0.f;
+    float f1[4], f2[4];
+    row_broadcast(s1, f1);
+    row_broadcast(s2, f2);
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+      for (int s = 0; s < CG; ++s) gb[s][b] = fmaf(f1[b], gt[s][b], f2[b] * gb[s][b]);
+  }
+  if (range.y > range.x) stage_load(range, staged);  // its records travel while the prologue ends
+  // the gradients in three bf16 parts that sum to them exactly (top, middle and
+  // last 8 significant bits)
+  uint32_t gq[KS][3][4][KW] = {};
+  auto split_operands = [&]() {
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+      for (int s = 0; s < CG; s += 2) {
+        float x = gb[s][b], y = gb[s + 1 < CGA ? s + 1 : 0][b];
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+          gq[s / 8][q][b][(s % 8) / 2] =
+              __builtin_amdgcn_perm(__float_as_uint(y), __float_as_uint(x), 0x07060302u);  // the top halves
+          x -= __uint_as_float(__float_as_uint(x) & 0xffff0000u);
+          y -= __uint_as_float(__float_as_uint(y) & 0xffff0000u);
+        }
+      }
+  };
+  if constexpr (D > 0) split_operands();
+  // list positions this wave must visit: below the largest saved length
+  uint32_t wave_max = last;
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1)
+    wave_max = max(wave_max, static_cast<uint32_t>(__shfl_xor(wave_max, off, kWave)));
+  bool nonfinite = !(finite_bits(gC[0]) && finite_bits(gC[1]) && finite_bits(gC[2]) && finite_bits(GZ));
+  // FEATGRAD: B operands of the feature sums: channel 16 bl + l % 16 of pixel
+  // 16 (l / 16) + i, exchanged through LDS
+  float gB[NBL][16] = {};
+  if constexpr (FEATGRAD) {
+    if (have_gf) {
+      float* gf = s_u.gf[wave];
+#pragma unroll
+      for (int b = 0; b < 4; ++b)
+#pragma unroll
+        for (int s = 0; s < CG; ++s) gf[(16 * b + (lane & 15)) * GS + CG * (lane >> 4) + s] = gb[s][b];
+      wave_lds_fence();
+#pragma unroll
+      for (int bl = 0; bl < NBL; ++bl)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          const int c = 16 * bl + (lane & 15);
+          if (c < D) gB[bl][i] = gf[(16 * (lane >> 4) + i) * GS + c];
+        }
+#pragma unroll 4
+      for (int c = 0; c < D; ++c) nonfinite |= !finite_bits(gf[lane * GS + c]);
+    }
+  }
+  __syncthreads();  // s_max cleared; the walk's staging takes the LDS
   if (lane == 0) atomicMax(&s_max, wave_max);
   if constexpr (RES) {
-    // this tile's loss share, summed in a fixed order (lanes, then waves)
-    lsum = wave_sum(lsum);
+    // this item's loss share, summed in a fixed order (lanes, then waves)
+    lsum = wave_sum(lsum * a.res_inv_hw);
     if (lane == 0) s_lw[wave] = lsum;
+  }
+  const uint64_t bad_pix = __ballot(nonfinite);
+  const bool bad = bad_pix != 0;  // uniform
+  {
+    const int at = (lane >> 3) * kBwdGcRow + (lane & 7);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) s_gc[wave][c][at] = gC[c];
+    if constexpr (!PO) s_gc[wave][PO ? 0 : 3][at] = GZ;
+  }
+  if constexpr (FEATGRAD) {
+    for (int e = tid; e < NB * GS; e += NT) s_gfe[e] = 0.f;
   }
   __syncthreads();
   if constexpr (RES) {
@@ -183,232 +508,264 @@ __device__ __forceinline__ void blend_bwd_item(const BackArgs& a, const int item
       float t = 0.f;
 #pragma unroll
       for (int w = 0; w < NW; ++w) t += s_lw[w];
-      a.res_part[static_cast<int64_t>(pose) * a.c.tiles_per_pose + tile] = t;
+      a.res_part[(static_cast<int64_t>(pose) * a.c.tiles_per_pose + tile) * Sh::kParts + part] = t;
     }
   }
   const uint32_t n_max = s_max;
   if (n_max == 0) return;
+
+  float S = gT * Tf;  // the suffix sum, from the outputs' direct dependence on the final transmittance
 
   // batches back to front; positions are relative to range.x
   const int n_batches = static_cast<int>((n_max + NB - 1) / NB);
   for (int bi = n_batches - 1; bi >= 0; --bi) {
     const uint32_t b0 = static_cast<uint32_t>(bi) * NB;
     const int nb = static_cast<int>(min(static_cast<uint32_t>(NB), n_max - b0));
+    if (staged != b0) {
+      stage_index(range, b0);
+      stage_load(range, b0);
+    }
+    stage_store(nb);
+    __syncthreads();
+    // the batch's splats that meet this wave's block and lie below its largest
+    // saved length, as a mask (the walk) and a list, back to front (the
+    // per-lane lookups)
+    uint64_t todo;
+    int n_mine;
     {
-      const int e = tid % NB, part = tid / NB;
-      if (e < nb) {
-        const uint32_t lv = a.list[range.x + b0 + e];
-        const uint32_t gid = a.list_gid[range.x + b0 + e];
-        const uint32_t r = lv & kRecMask;
-        const float4* sp = reinterpret_cast<const float4*>(a.recs + r);
-        const float4 g1 = sp[1];
-        if (part == 0) {
-          s_geo[e] = sp[0];
-          s_opz[e] = g1;
-          s_col[e] = sp[2];
-          s_rec[e] = r;
-          s_mask[e] = static_cast<uint8_t>(lv >> kRecBits);  // waves whose block the support meets
-        }
-        if constexpr (DV > 0) {
-          if (part < PARTS) {
-            constexpr int QV = DV / PARTS;
-            const uint4* fv = reinterpret_cast<const uint4*>(a.feat) + static_cast<int64_t>(gid) * DV + part * QV;
+      const bool hit = lane < nb && b0 + lane < wave_max && ((s_mask[lane] >> mask_bit) & 1u);
+      todo = __ballot(hit);
+      n_mine = __popcll(todo);
+      if (hit) s_list[wave][__popcll(todo >> lane) - 1] = static_cast<uint8_t>(lane);
+      if (lane == 0) s_hits[wave] = todo;
+    }
+    wave_lds_fence();
+    // the next round's splats travel while this one's are walked
+    if (bi > 0) {
+      staged = b0 - NB;
+      stage_index(range, staged);
+      stage_load(range, staged);
+    }
+    for (int g0 = 0; g0 < n_mine; g0 += kBwdGroup) {
+      // h's feature part of 16 splats: hq[q] for this lane's pixel
+      float hq[kBwdGroup];
 #pragma unroll
-            for (int q = 0; q < QV; ++q) {
-              const uint4 f = fv[q];
-              if constexpr (MF) {
-                reinterpret_cast<uint4*>(&s_fb[e * FBS])[part * QV + q] = f;
+      for (int q = 0; q < kBwdGroup; ++q) hq[q] = 0.f;
+      if constexpr (D > 0) {
+        const int js = s_list[wave][min(g0 + (lane & 15), n_mine - 1)];
+        floatx4 acc[4] = {};
+        const uint32_t* fw = &s_fb[js * FBS + (CG / 2) * (lane >> 4)];
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+          uint32_t av[KW] = {};
+          if constexpr (KW == 4) {
+            const uint4 w = reinterpret_cast<const uint4*>(fw)[ks];
+            av[0] = w.x; av[1] = w.y; av[KW - 2] = w.z; av[KW - 1] = w.w;
+          } else {
+            av[0] = fw[0];
+            if constexpr (CG > 2) av[1] = fw[1];
+          }
+#pragma unroll
+          for (int q = 2; q >= 0; --q)
+#pragma unroll
+            for (int b = 0; b < 4; ++b) {
+              if constexpr (KW == 4) {
+                bf16x8 A, B;
+                __builtin_memcpy(&A, av, 16);
+                __builtin_memcpy(&B, gq[ks][q][b], 16);
+                acc[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A, B, acc[b], 0, 0, 0);
               } else {
-                float4* dst = reinterpret_cast<float4*>(&s_f[e * FS + 8 * (part * QV + q)]);
-                dst[0] = make_float4(bf16_lo(f.x), bf16_hi(f.x), bf16_lo(f.y), bf16_hi(f.y));
-                dst[1] = make_float4(bf16_lo(f.z), bf16_hi(f.z), bf16_lo(f.w), bf16_hi(f.w));
+                shortx4 A, B;
+                __builtin_memcpy(&A, av, 8);
+                __builtin_memcpy(&B, gq[ks][q][b], 8);
+                acc[b] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(A, B, acc[b], 0, 0, 0);
+              }
+            }
+        }
+        // lane l, register r of block b: splat 4 (l / 16) + r, pixel
+        // 16 b + l % 16 -> this lane's pixel
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          uint32_t t[4];
+#pragma unroll
+          for (int b = 0; b < 4; ++b) t[b] = __float_as_uint(acc[b][r]);
+          transpose_rows(t[0], t[1], t[2], t[3]);
+#pragma unroll
+          for (int k = 0; k < 4; ++k) hq[4 * k + r] = __uint_as_float(t[k]);
+        }
+      }
+#pragma unroll
+      for (int half = 0; half < 2; ++half) {
+        const int h0 = g0 + half * kBwdHalf;
+        if (h0 >= n_mine) break;  // uniform
+        const int wrow = FEATGRAD ? half * kBwdHalf : 0;
+        // a splat's geometry and colour are read a step ahead: a step that waits
+        // for its own LDS reads takes twice as long
+        int jn = 63 - __builtin_clzll(todo);
+        float4 geo_n = s_sp[jn][0], opz_n = s_sp[jn][1], col_n = s_sp[jn][2];
+#pragma unroll
+        for (int q = 0; q < kBwdHalf; ++q) {
+          if (todo == 0) break;  // uniform
+          const int jj = jn;
+          const float4 geo = geo_n, opz = opz_n, col = col_n;
+          todo &= ~(1ull << jj);
+          if (q + 1 < kBwdHalf) {
+            jn = todo ? 63 - __builtin_clzll(todo) : jj;
+            geo_n = s_sp[jn][0];
+            opz_n = s_sp[jn][1];
+            col_n = s_sp[jn][2];
+            __atomic_signal_fence(__ATOMIC_SEQ_CST);  // issued here, not where they are used
+          }
+          const float dx = pxf - geo.x, dy = pyf - geo.y;
+          const float power = pair_power(dx, dy, geo.z, geo.w, opz.x);
+          const float oG = opz.y * __expf(power);
+          const float alpha = fminf(kAlphaMax, oG);
+          float dpow = 0.f, w = 0.f;
+          if (b0 + jj < last && !(power > 0.f) && !(alpha < kAlphaMin)) {
+            const float iom = __builtin_amdgcn_rcpf(1.f - alpha);  // alpha <= 0.99
+            T *= iom;
+            w = alpha * T;
+            // gradient arithmetic (not a blend decision): fused multiply-adds
+            float h = fmaf(gC[0], col.x, fmaf(gC[1], col.y, fmaf(gC[2], col.z, hq[half * kBwdHalf + q])));
+            if constexpr (!PO) h = fmaf(GZ, opz.z, h);
+            const float dA = fmaf(T, h, -(S * iom));
+            S = fmaf(w, h, S);
+            dpow = oG <= kAlphaMax ? dA * alpha : 0.f;
+          }
+          s_d[wave][q][lane] = dpow;
+          s_w[wave][wrow + q][lane] = w;
+        }
+        wave_lds_fence();
+        // transposed: lane l takes splat l % 8's pixel row l / 8 of the block
+        {
+          const int s = lane & 7, row = lane >> 3;
+          const int e = h0 + s;
+          const int slot = s_list[wave][min(e, n_mine - 1)];
+          const float2 uv = *reinterpret_cast<const float2*>(&s_sp[slot][0]);
+          const float x0 = static_cast<float>(bx0) + 0.5f - uv.x;
+          const float dy = static_cast<float>(by0 + row) + 0.5f - uv.y;
+          float m0 = 0.f, m1 = 0.f, m2 = 0.f, c[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (int i4 = 0; i4 < 2; ++i4) {
+            const float4 d4 = *reinterpret_cast<const float4*>(&s_d[wave][s][8 * row + 4 * i4]);
+            const float4 w4 = *reinterpret_cast<const float4*>(&s_w[wave][wrow + s][8 * row + 4 * i4]);
+            const float dv[4] = {d4.x, d4.y, d4.z, d4.w}, wv[4] = {w4.x, w4.y, w4.z, w4.w};
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              const float dx = x0 + static_cast<float>(4 * i4 + i);
+              const float t = dv[i] * dx;
+              m0 += dv[i];
+              m1 += t;
+              m2 = fmaf(t, dx, m2);
+            }
+#pragma unroll
+            for (int k = 0; k < (PO ? 3 : 4); ++k) {
+              const float4 g4 = *reinterpret_cast<const float4*>(&s_gc[wave][k][row * kBwdGcRow + 4 * i4]);
+              const float gv[4] = {g4.x, g4.y, g4.z, g4.w};
+              if (!bad) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) c[k] = fmaf(wv[i], gv[i], c[k]);
+              } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) c[k] = wv[i] != 0.f ? fmaf(wv[i], gv[i], c[k]) : c[k];
               }
             }
           }
+          const float v[8] = {m1, m0 * dy, m2, m1 * dy, m0 * dy * dy, c[0], c[1], c[2]};
+          const float tot = octet_scatter8(v, lane);
+          const int k = lane >> 3;
+          if (e < n_mine) s_g[wave][k * GR + slot] = tot;
+          if constexpr (!PO) {
+            const float t2 = octet_sum2(m0, c[3]);
+            if ((lane & 31) < 8 && e < n_mine) s_g[wave][(lane < 32 ? NV - 2 : NV - 1) * GR + slot] = t2;
+          }
         }
+        wave_lds_fence();  // the rows are rewritten by the next half
       }
-    }
-    __syncthreads();
-    // compact the batch to the entries touching this wave's block and below
-    // its largest saved length (in list order)
-    int n_mine = 0;
-    for (int c0 = 0; c0 < nb; c0 += kWave) {
-      const int ce = c0 + lane;
-      const bool hit = ce < nb && b0 + ce < wave_max && ((s_mask[ce] >> wave) & 1u);
-      const uint64_t bal = __ballot(hit);
-      if (hit) s_list[wave][n_mine + __popcll(bal & ((1ull << lane) - 1ull))] = static_cast<uint16_t>(ce);
-      n_mine += __popcll(bal);
-    }
-    __builtin_amdgcn_wave_barrier();
-    // the next entry's index is read one step ahead
-    int jn = n_mine > 0 ? static_cast<int>(s_list[wave][n_mine - 1]) : 0;
-    for (int ii = n_mine - 1; ii >= 0; --ii) {
-      if constexpr (MF) {
-        if (ii == n_mine - 1 || (ii + 1) % kHGroup == 0) {
-          // H for the group of compacted entries [g0, g0 + 32) holding ii
-          const int g0 = ii / kHGroup * kHGroup;
-          const int row = lane & 31, half = lane >> 5;
-          const int e = g0 + row;
-          const int js = e < n_mine ? static_cast<int>(s_list[wave][e]) : -1;
-          floatx16 acc0 = {}, acc1 = {};
+      if constexpr (FEATGRAD) {
+        // rows of splats past the list hold stale weights: their sums are dropped
+        const int q4 = lane >> 4, ch = lane & 15;
+        floatx4 acc[NBL] = {};
 #pragma unroll
-          for (int ks = 0; ks < 4; ++ks) {
-            uint2 av = make_uint2(0u, 0u);
-            if (js >= 0) av = *reinterpret_cast<const uint2*>(&s_fb[js * FBS + 4 * ks + 2 * half]);
-            shortx4 A;
-            __builtin_memcpy(&A, &av, 8);
-            // B: this lane's pixel gradient, channels 8 ks .. 8 ks + 7, split
-            // into three exact bf16 parts; lane l supplies channels
-            // 8 ks + 4 (l / 32) + 0..3 of pixel l % 32 (block 0) and of pixel
-            // 32 + l % 32 (block 1): its own half of the channels for its own
-            // block, the partner lane's (l ^ 32) for the other, exchanged with
-            // one lane-half swap per word
-            float r[8];
+        for (int i4 = 0; i4 < 4; ++i4) {
+          const float4 w4 = *reinterpret_cast<const float4*>(&s_w[wave][ch][16 * q4 + 4 * i4]);
+          const float wv[4] = {w4.x, w4.y, w4.z, w4.w};
 #pragma unroll
-            for (int c = 0; c < 8; ++c) {
-              r[c] = gF[0][8 * ks + c];
-              // keeps the split inside the group loop (recomputed per group)
-              // instead of hoisted into 48 live registers for the whole walk
-              asm volatile("" : "+v"(r[c]));
+          for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int bl = 0; bl < NBL; ++bl) {
+              float g = gB[bl][4 * i4 + i];
+              if (bad) g = ((bad_pix >> (16 * q4 + 4 * i4 + i)) & 1u) ? 0.f : g;
+              acc[bl] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[i], g, acc[bl], 0, 0, 0);
             }
+        }
+        // lane l, register r: splat 4 (l / 16) + r, channel 16 bl + l % 16
+        if (bad) {  // uniform; pixels with non-finite gradients, for the splats blended there
 #pragma unroll
-            for (int part = 0; part < 3; ++part) {
-              uint32_t hw[4];  // bf16 pairs: channels (0,1) (2,3) (4,5) (6,7)
+          for (int i = 0; i < 16; ++i)
+            for (int k = 0; k < 4; ++k) {
+              const int p = 16 * k + i;
+              if (!((bad_pix >> p) & 1u)) continue;
 #pragma unroll
-              for (int c = 0; c < 4; ++c) {
-                const uint32_t x = __float_as_uint(r[2 * c]) & 0xffff0000u;
-                const uint32_t y = __float_as_uint(r[2 * c + 1]) & 0xffff0000u;
-                hw[c] = (x >> 16) | y;
-                if (part < 2) {
-                  r[2 * c] -= __uint_as_float(x);
-                  r[2 * c + 1] -= __uint_as_float(y);
+              for (int bl = 0; bl < NBL; ++bl) {
+                const float g = __shfl(gB[bl][i], 16 * k + ch, kWave);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                  const float wv = s_w[wave][4 * q4 + r][p];
+                  if (wv != 0.f) acc[bl][r] = fmaf(wv, g, acc[bl][r]);
                 }
               }
-              uint32_t b0w[2], b1w[2];
-#pragma unroll
-              for (int w = 0; w < 2; ++w) {
-                const auto sw = __builtin_amdgcn_permlane32_swap(hw[w], hw[2 + w], false, false);
-                b0w[w] = sw[0];
-                b1w[w] = sw[1];
-              }
-              shortx4 B0, B1;
-              __builtin_memcpy(&B0, b0w, 8);
-              __builtin_memcpy(&B1, b1w, 8);
-              acc0 = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(A, B0, acc0, 0, 0, 0);
-              acc1 = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(A, B1, acc1, 0, 0, 0);
             }
-          }
-          // accumulator layout: lane l, register r holds row 8 (r/4) + 4 (l/32)
-          // + r%4 (group entry) of column l % 32 (pixel, + 32 for acc1)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const int hr = 8 * (r / 4) + 4 * half + (r % 4);
-            s_h[MF ? wave : 0][hr][row] = acc0[r];
-            s_h[MF ? wave : 0][hr][32 + row] = acc1[r];
-          }
-          __builtin_amdgcn_wave_barrier();
         }
-      }
-      const int jj = __builtin_amdgcn_readfirstlane(jn);
-      jn = ii > 0 ? static_cast<int>(s_list[wave][ii - 1]) : 0;
-      const uint32_t pos = b0 + jj;
-      const float4 geo = s_geo[jj];
-      const float4 opz = s_opz[jj];
-      const float4 col = s_col[jj];
-      float g[10];
 #pragma unroll
-      for (int q = 0; q < 10; ++q) g[q] = 0.f;
-      float gfe[FEATGRAD ? DD : 1];
-      if constexpr (FEATGRAD) {
+        for (int r = 0; r < 4; ++r) {
+          const int e = g0 + 4 * q4 + r;
+          if (e < n_mine) {
+            const int slot = s_list[wave][e];
 #pragma unroll
-        for (int d = 0; d < DD; ++d) gfe[d] = 0.f;
-      }
-      bool any = false;
-#pragma unroll
-      for (int k = 0; k < PPT; ++k) {
-        if (pos >= last[k]) continue;
-        const float dx = pxf[k] - geo.x, dy = pyf[k] - geo.y;
-        const float power = pair_power(dx, dy, geo.z, geo.w, opz.x);
-        if (power > 0.f) continue;
-        const float G = __expf(power);
-        const float alpha = fminf(kAlphaMax, opz.y * G);
-        if (alpha < kAlphaMin) continue;
-        any = true;
-        const float om = 1.f - alpha;
-        const float iom = __builtin_amdgcn_rcpf(om);  // 1/(1 - alpha), alpha <= 0.99
-        const float Tj = T[k] * iom;
-        const float w = alpha * Tj;
-        // gradient arithmetic (not a blend decision): fused multiply-adds
-        float h = fmaf(gC[k][0], col.x, fmaf(gC[k][1], col.y, fmaf(gC[k][2], col.z, GZ[k] * opz.z)));
-        if constexpr (MF) {
-          h += s_h[MF ? wave : 0][ii % kHGroup][lane];
-        } else if constexpr (D > 0) {
-          const float4* fq = reinterpret_cast<const float4*>(&s_f[jj * FS]);
-#pragma unroll
-          for (int q = 0; q < D / 4; ++q) {
-            const float4 f = fq[q];
-            h = fmaf(gF[k][4 * q + 0], f.x, h);
-            h = fmaf(gF[k][4 * q + 1], f.y, h);
-            h = fmaf(gF[k][4 * q + 2], f.z, h);
-            h = fmaf(gF[k][4 * q + 3], f.w, h);
+            for (int bl = 0; bl < NBL; ++bl)
+              if (16 * bl + ch < D) atomicAdd(&s_gfe[slot * GS + 16 * bl + ch], acc[bl][r]);
           }
         }
-        const float dA = fmaf(Tj, h, -(fmaf(gT[k], Tf[k], S[k]) * iom));
-        S[k] = fmaf(w, h, S[k]);
-        T[k] = Tj;
-        g[7] = fmaf(w, gC[k][0], g[7]);
-        g[8] = fmaf(w, gC[k][1], g[8]);
-        g[9] = fmaf(w, gC[k][2], g[9]);
-        if constexpr (!PO) g[6] = fmaf(w, GZ[k], g[6]);
-        if (opz.y * G <= kAlphaMax) {
-          const float dpow = dA * alpha;
-          const float hx = -0.5f * dpow * dx, hy = -0.5f * dpow * dy;
-          if constexpr (!PO) g[5] = fmaf(dA, G, g[5]);
-          g[0] = fmaf(dpow, fmaf(geo.z, dx, geo.w * dy), g[0]);
-          g[1] = fmaf(dpow, fmaf(geo.w, dx, opz.x * dy), g[1]);
-          g[2] = fmaf(hx, dx, g[2]);
-          g[3] = fmaf(2.f * hx, dy, g[3]);
-          g[4] = fmaf(hy, dy, g[4]);
-        }
-        if constexpr (FEATGRAD) {
-#pragma unroll
-          for (int d = 0; d < DD; ++d) gfe[d] = fmaf(w, gF[k][d], gfe[d]);
-        }
-      }
-      if (!__any(any)) continue;
-      if constexpr (PO) wave_add8(g, s_g[jj]);
-      else wave_add10(g, s_g[jj]);
-      if constexpr (FEATGRAD) {
-#pragma unroll
-        for (int d = 0; d < DD; ++d) gfe[d] = wave_sum(gfe[d]);
-        if (lane == 0) {
-          float* fd = a.g_featvec + static_cast<int64_t>(__float_as_uint(opz.w)) * D;
-#pragma unroll
-          for (int d = 0; d < DD; ++d) atomicAdd(fd + d, gfe[d]);
-        }
+        wave_lds_fence();
       }
     }
     __syncthreads();
-    // one global atomic per nonzero sum of the batch; clear for the next
-    for (int e = tid; e < nb * 10; e += NT) {
-      const int slot = e / 10, q = e - slot * 10;
-      const float v = s_g[slot][q];
-      if (v != 0.f) {
-        atomicAdd(a.g_rec + static_cast<int64_t>(s_rec[slot]) * kGradRecStride + q, v);
-        s_g[slot][q] = 0.f;
+    // one global atomic per nonzero sum of the round: the waves that hit the
+    // splat, in order
+    for (int e = tid; e < nb * NV; e += NT) {
+      const int slot = e / NV, k = e - slot * NV;
+      float v = 0.f;
+#pragma unroll
+      for (int w = 0; w < NW; ++w)
+        if ((s_hits[w] >> slot) & 1u) v += s_g[w][k * GR + slot];
+      // rows: d dx, d dy, d dx^2, d dx dy, d dy^2, w gC (3), d, w gZ
+      const int at = k < 5 ? k : (k < 8 ? k + 2 : k - 3);
+      if (v != 0.f)
+        atomicAdd(a.g_rec + static_cast<int64_t>(__float_as_uint(s_sp[slot][3].x)) * kGradRecStride + at, v);
+    }
+    if constexpr (FEATGRAD) {
+      for (int e = tid; e < nb * D; e += NT) {
+        const int slot = e / D, d = e - slot * D;
+        const float v = s_gfe[slot * GS + d];
+        if (v != 0.f) {
+          atomicAdd(a.g_featvec + static_cast<int64_t>(__float_as_uint(s_sp[slot][1].w)) * D + d, v);
+          s_gfe[slot * GS + d] = 0.f;
+        }
       }
     }
-    __syncthreads();  // the next batch's staging overwrites s_rec
+    __syncthreads();  // the next batch's staging overwrites s_sp
   }
 }
 
-// One workgroup per (pose, tile) item, or (PERSIST) a grid of workgroups
-// claiming runs of kQueueChunk items from a device counter until it passes
-// the item count.
-template <int TILE, int D, bool FEATGRAD, bool RES, bool MFH, bool PERSIST, bool PO = false>
-__global__ __launch_bounds__(BlendShape<TILE>::kThreads) void blend_bwd_kernel(BackArgs a) {
-  if (a.flags[0] & 3) return;
+// One workgroup per item ((pose, tile), or a quadrant of a 32-pixel tile), or
+// (PERSIST) a grid of workgroups claiming runs of kQueueChunk items from a
+// device counter until it passes the item count.
+template <int TILE, int D, bool FEATGRAD, bool RES, bool PERSIST, bool PO = false>
+__global__ __launch_bounds__(BwdShape<TILE>::kThreads, (PO && D <= 32 && !PERSIST && TILE != 8) ? 4 : 1) void
+blend_bwd_kernel(BackArgs a) {
   if constexpr (PERSIST) {
+    if (a.flags[0] & 3) return;
     __shared__ int s_item;
     for (;;) {
       if (threadIdx.x == 0) s_item = static_cast<int>(atomicAdd(a.queue, static_cast<uint32_t>(kQueueChunk)));
@@ -418,12 +775,12 @@ __global__ __launch_bounds__(BlendShape<TILE>::kThreads) void blend_bwd_kernel(B
       if (first >= a.n_items) break;
       const int last = min(first + kQueueChunk, a.n_items);
       for (int item = first; item < last; ++item) {
-        blend_bwd_item<TILE, D, FEATGRAD, RES, MFH, PO>(a, item);
+        blend_bwd_item<TILE, D, FEATGRAD, RES, PO>(a, item);
         __syncthreads();  // the item's LDS is reused by the next one
       }
     }
   } else {
-    blend_bwd_item<TILE, D, FEATGRAD, RES, MFH, PO>(a, xcd_item(blockIdx.x, gridDim.x));
+    blend_bwd_item<TILE, D, FEATGRAD, RES, PO>(a, xcd_item(blockIdx.x, gridDim.x));
   }
 }
 
@@ -448,55 +805,48 @@ void launch_loss_reduce(const float* part, int32_t tiles_per_pose, int32_t P, fl
 }
 
 template <int TILE, int D, bool PERSIST>
-static void launch_bwd_tdp(const BackArgs& a, int items, hipStream_t s) {
-  constexpr int NT = BlendShape<TILE>::kThreads;
-  // the feature term on the matrix cores: 32 channels, one pixel per lane,
-  // no per-Gaussian feature gradient
-  constexpr bool MFOK = D == 32 && BlendShape<TILE>::kPPT == 1;
-  const bool mf = MFOK && a.feat_mfma && !a.g_featvec;
+static void launch_bwd_tdp(const BackArgs& a, int n_ctas, hipStream_t s) {
+  constexpr int NT = BwdShape<TILE>::kThreads;
+  constexpr bool F = D > 0;  // without features there is no feature gradient
   if (a.res_rgb_t) {
-    if (a.g_featvec)
-      hipLaunchKernelGGL((blend_bwd_kernel<TILE, D, true, true, false, PERSIST>), dim3(items), dim3(NT), 0, s, a);
-    else if (mf)
-      hipLaunchKernelGGL((blend_bwd_kernel<TILE, D, false, true, MFOK, PERSIST>), dim3(items), dim3(NT), 0, s, a);
+    if (F && a.g_featvec)
+      hipLaunchKernelGGL((blend_bwd_kernel<TILE, D, F, true, PERSIST>), dim3(n_ctas), dim3(NT), 0, s, a);
     else if (a.pose_only)
-      hipLaunchKernelGGL((blend_bwd_kernel<TILE, D, false, true, false, PERSIST, true>), dim3(items), dim3(NT), 0, s,
-                         a);
+      hipLaunchKernelGGL((blend_bwd_kernel<TILE, D, false, true, PERSIST, true>), dim3(n_ctas), dim3(NT), 0, s, a);
     else
-      hipLaunchKernelGGL((blend_bwd_kernel<TILE, D, false, true, false, PERSIST>), dim3(items), dim3(NT), 0, s, a);
+      hipLaunchKernelGGL((blend_bwd_kernel<TILE, D, false, true, PERSIST>), dim3(n_ctas), dim3(NT), 0, s, a);
   } else {
-    if (a.g_featvec)
-      hipLaunchKernelGGL((blend_bwd_kernel<TILE, D, true, false, false, PERSIST>), dim3(items), dim3(NT), 0, s, a);
-    else if (mf)
-      hipLaunchKernelGGL((blend_bwd_kernel<TILE, D, false, false, MFOK, PERSIST>), dim3(items), dim3(NT), 0, s, a);
+    if (F && a.g_featvec)
+      hipLaunchKernelGGL((blend_bwd_kernel<TILE, D, F, false, PERSIST>), dim3(n_ctas), dim3(NT), 0, s, a);
     else
-      hipLaunchKernelGGL((blend_bwd_kernel<TILE, D, false, false, false, PERSIST>), dim3(items), dim3(NT), 0, s, a);
+      hipLaunchKernelGGL((blend_bwd_kernel<TILE, D, false, false, PERSIST>), dim3(n_ctas), dim3(NT), 0, s, a);
   }
 }
 
 template <int TILE, int D>
-static void launch_bwd_td(const BackArgs& a, int items, hipStream_t s) {
+static void launch_bwd_td(const BackArgs& a, hipStream_t s) {
   if (a.schedule != kSchedGrid) launch_bwd_tdp<TILE, D, true>(a, a.n_ctas, s);
-  else launch_bwd_tdp<TILE, D, false>(a, items, s);
+  else launch_bwd_tdp<TILE, D, false>(a, a.n_items, s);
 }
 
 template <int TILE>
-static void launch_bwd_t(const BackArgs& a, int items, hipStream_t s) {
+static void launch_bwd_t(const BackArgs& a, hipStream_t s) {
   switch (a.D) {
-    case 0: launch_bwd_td<TILE, 0>(a, items, s); break;
-    case 8: launch_bwd_td<TILE, 8>(a, items, s); break;
-    case 16: launch_bwd_td<TILE, 16>(a, items, s); break;
-    case 32: launch_bwd_td<TILE, 32>(a, items, s); break;
-    default: launch_bwd_td<TILE, 64>(a, items, s); break;
+    case 0: launch_bwd_td<TILE, 0>(a, s); break;
+    case 8: launch_bwd_td<TILE, 8>(a, s); break;
+    case 16: launch_bwd_td<TILE, 16>(a, s); break;
+    case 32: launch_bwd_td<TILE, 32>(a, s); break;
+    default: launch_bwd_td<TILE, 64>(a, s); break;
   }
 }
 
+int blend_bwd_parts(int tile) { return tile == 32 ? BwdShape<32>::kParts : 1; }
+
 void launch_blend_bwd(const BackArgs& a, hipStream_t s) {
-  const int items = a.P * a.c.tiles_per_pose;
   switch (a.c.tile) {
-    case 8: launch_bwd_t<8>(a, items, s); break;
-    case 32: launch_bwd_t<32>(a, items, s); break;
-    default: launch_bwd_t<16>(a, items, s); break;
+    case 8: launch_bwd_t<8>(a, s); break;
+    case 32: launch_bwd_t<32>(a, s); break;
+    default: launch_bwd_t<16>(a, s); break;
   }
 }
 
@@ -581,9 +931,13 @@ __device__ __forceinline__ void record_grad(const ProjBackArgs& a, const int pos
   {
     const int64_t idx = static_cast<int64_t>(pose) * a.rec_cap + slot;
     const float* gr = a.g_rec + idx * kGradRecStride;
-    const float g_u = gr[0], g_v = gr[1], g_ca = gr[2], g_cb = gr[3], g_cc = gr[4], g_o = gr[5], g_z = gr[6];
-    const float gcol[3] = {gr[7], gr[8], gr[9]};
     const Splat sp = a.recs[idx];
+    // from the moments of dL/dpower over the splat's pixels: power is
+    // -(ca dx^2 + cc dy^2) / 2 - cb dx dy with dx, dy from the mean, and
+    // alpha = o e^power
+    const float g_u = fmaf(sp.ca, gr[0], sp.cb * gr[1]), g_v = fmaf(sp.cb, gr[0], sp.cc * gr[1]);
+    const float g_ca = -0.5f * gr[2], g_cb = -gr[3], g_cc = -0.5f * gr[4], g_o = gr[5] / sp.o, g_z = gr[6];
+    const float gcol[3] = {gr[7], gr[8], gr[9]};
     const int64_t i = sp.gid;
     const float* Pm = a.poses + 12 * pose;
     const float mu[3] = {a.g.means[3 * i], a.g.means[3 * i + 1], a.g.means[3 * i + 2]};

@@ -252,7 +252,7 @@ hgsr_status for_each_render_buf(hgsr_ctx* c, int P, const CamArgs& cam, bool lsd
   TRY(f(c->finalT, npix * sizeof(float)));
   TRY(f(c->nused, npix * sizeof(uint32_t)));
   TRY(f(c->part_vis, std::max(P, 1) * sizeof(uint64_t)));
-  TRY(f(c->loss_part, ntile * sizeof(float)));
+  TRY(f(c->loss_part, ntile * blend_bwd_parts(cam.tile) * sizeof(float)));
   if (lsd) {
     TRY(f(c->rec_keys, nrec * sizeof(uint32_t)));
     TRY(f(c->rec_offsets, nrec * sizeof(uint32_t)));
@@ -1219,11 +1219,6 @@ static hgsr_status backward_impl(hgsr_ctx* c, const hgsr_grad_outputs* go, const
   BackArgs b;
   b.c = c->cam;
   b.P = P;
-  // the backward's feature term on the matrix cores only when the render
-  // asked for the matrix-core feature sum (measured slower than the VALU dot
-  // product on the refinement workload: the per-group matrix products and
-  // their LDS staging outweigh the 32 FMAs per visited pair)
-  b.feat_mfma = c->opts.feat_accum == HGSR_FEAT_MFMA ? 1 : 0;
   b.ranges = c->ranges.as<uint2>();
   b.list = c->sorted;
   b.list_gid = c->sorted_gid;
@@ -1252,12 +1247,14 @@ static hgsr_status backward_impl(hgsr_ctx* c, const hgsr_grad_outputs* go, const
   b.res_part = c->loss_part.as<float>();
   b.pose_only = rt && !gr->opacities ? 1 : 0;
   b.schedule = c->opts.schedule;
-  b.n_items = static_cast<int32_t>(static_cast<int64_t>(P) * c->cam.tiles_per_pose);
+  b.share_target = b.schedule == HGSR_SCHED_GRID && rt && rt->shared_target && P > 1 ? 1 : 0;
+  const int parts = blend_bwd_parts(c->cam.tile);
+  b.n_items = P * c->cam.tiles_per_pose * parts;
   b.n_ctas = static_cast<int32_t>(std::min<int64_t>(b.n_items, persistent_ctas(c, c->cam.tile)));
   b.queue = reinterpret_cast<uint32_t*>(misc + kQueueBwd);
   if (b.schedule != HGSR_SCHED_GRID) launch_fill_u32(b.queue, 0u, 1, s);
   launch_blend_bwd(b, s);
-  if (rt) launch_loss_reduce(c->loss_part.as<float>(), c->cam.tiles_per_pose, P, loss, s);
+  if (rt) launch_loss_reduce(c->loss_part.as<float>(), c->cam.tiles_per_pose * parts, P, loss, s);
   hipEvent_t e1 = stamp(c, s);
   ProjBackArgs pb;
   pb.g = make_gauss(c->g);

@@ -99,7 +99,6 @@ struct BlendArgs {
 struct BackArgs {
   CamArgs c;
   int32_t P;
-  int32_t feat_mfma;         // feature term of h on the matrix cores (D 32, one pixel per lane)
   const uint2* ranges;
   const uint32_t* list;
   const uint32_t* list_gid;  // Gaussian index of each list entry
@@ -111,7 +110,8 @@ struct BackArgs {
   // blend backward forms eight of the ten per-splat sums (no opacity or depth)
   int32_t pose_only;
   int32_t schedule;          // kSchedGrid, or a persistent queue of (pose, tile) items
-  int32_t n_items;
+  int32_t share_target;      // grid schedule, one residual target for all poses: poses interleaved by tile runs
+  int32_t n_items;           // workgroups' items: (pose, tile) times blend_bwd_parts(tile)
   int32_t n_ctas;            // workgroups of the persistent launch
   uint32_t* queue;           // item counter (zero before the launch)
   const float* fwd_depth;
@@ -121,12 +121,14 @@ struct BackArgs {
   const float* g_depth;
   const float* g_alpha;
   const float* g_feat;
-  float* g_rec;              // per record: du dv da db dc do dz dr dg db (+2 pad)
+  // per record, d = dL/dpower and w = alpha T at a pixel, sums over pixels of
+  // d dx, d dy, d dx^2, d dx dy, d dy^2, d, w gZ, w gC (3) (+2 pad)
+  float* g_rec;
   float* g_featvec;          // n x D or null
   const int32_t* flags;
   // refinement residual formed per pixel in place of g_rgb / g_feat
   // (res_rgb_t != null): from the forward's rgb and feature outputs and the
-  // targets; the per-(pose, tile) loss shares go to res_part
+  // targets; the items' loss shares go to res_part
   const float* fwd_rgb;
   const void* fwd_feat;
   int32_t fwd_feat_bf16;
@@ -244,6 +246,7 @@ hipError_t probe_valu_rate(int n_cu, hipStream_t s, double* wave_fma_per_s);
 void launch_blend_fwd(const BlendArgs& a, int D, bool bf16_out, int n_ctas, hipStream_t s);
 
 // backward.hip
+int blend_bwd_parts(int tile);  // workgroups (and loss shares) per (pose, tile)
 void launch_blend_bwd(const BackArgs& a, hipStream_t s);
 void launch_project_bwd(const ProjBackArgs& a, hipStream_t s);
 void launch_zero_grad_rec(float* g, const uint32_t* pose_count, uint32_t rec_cap, int P, hipStream_t s);

@@ -487,3 +487,25 @@ def test_long_lists_give_every_record_its_own_sums(hg, D, tile):
             ref = g
         for k in want:
             assert _rel(g[k], ref[k]) < 1e-5, (k, t)
+
+
+@pytest.mark.parametrize("D,tile", [(8, 16), (32, 16), (32, 8), (64, 32)])
+def test_non_finite_output_gradients_stay_with_their_pixels(hg, D, tile):
+    """A NaN colour or feature gradient at one pixel makes exactly the
+    gradients non-finite that a finite one at that pixel makes non-zero: the
+    splats blended there."""
+    import torch
+    sc, P, cam = synth.tiny_scene(600, 131 + D, width=53, height=45, feat_dim=D, sh_degree=0)
+    scene = hg.GaussianScene.from_numpy(sc)
+    K = hg.Intrinsics.of(cam)
+    log(f"case: NaN gradients D={D} tile={tile}")
+    r = hg.Renderer()
+    out = r.render(scene, _t(P), K, tile=tile)
+    for name, want in (("rgb", "sh"), ("feat", "feat")):
+        g1 = torch.zeros_like(out[name])
+        g1[0, :, 21, 30] = 1.0
+        fin = r.backward({name: g1}, want=("sh", "feat"))[want].clone()
+        assert torch.isfinite(fin).all() and (fin != 0).any()
+        g1[0, :, 21, 30] = float("nan")
+        bad = r.backward({name: g1}, want=("sh", "feat"))[want]
+        assert torch.equal(~torch.isfinite(bad), fin != 0), name
