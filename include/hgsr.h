@@ -115,15 +115,14 @@ enum { HGSR_SCHED_GRID = 0, HGSR_SCHED_POSE_MAJOR = 1, HGSR_SCHED_TILE_MAJOR = 2
  * z below which a Gaussian is culled (0.2).  feat_out_bf16: write the feature
  * image as bfloat16 (FP32 accumulation).  lds_sort_cap: largest per-tile list
  * sorted in LDS (0 = default 4096; larger lists take a global-memory path).
- * feat_accum: how 32-channel features are summed at tile 8 and 16 --
- * HGSR_FEAT_AUTO (the autotuned choice, else the VALU), HGSR_FEAT_VALU
- * (per-pixel FMAs in blend order) or HGSR_FEAT_MFMA (per group of 8 splats,
- * a 32x8 by 8x64 matrix-core product of the bf16 features and the per-pixel
- * FP32 weights, each weight split exactly into three bf16 parts; the same
- * sum in another association order, colour, depth and alpha unchanged).  HGSR_FEAT_MFMA also moves the
- * backward's per-pair feature term (the pixel's feature gradient dotted with
- * the splat's feature) onto the matrix cores, per group of 32 splats; the
- * other settings keep it on the VALU. */
+ * feat_accum: how 32- and 64-channel features are summed --
+ * HGSR_FEAT_AUTO (the autotuned choice, else the matrix cores),
+ * HGSR_FEAT_VALU (per-pixel FMAs in blend order) or HGSR_FEAT_MFMA (per group
+ * of 16 splats, a 32x16 by 16x64 matrix-core product per 32 channels of the
+ * bf16 features and the per-pixel FP32 weights, each weight split exactly
+ * into three bf16 parts; the same sum in another association order, colour,
+ * depth and alpha unchanged).  8 and 16 channels are always FMAs in blend
+ * order.  The backward does not depend on it. */
 enum { HGSR_FEAT_AUTO = 0, HGSR_FEAT_VALU = 1, HGSR_FEAT_MFMA = 2 };
 
 typedef struct {
@@ -661,7 +660,7 @@ hgsr_status hgsr_debug_tile_lists(hgsr_ctx* ctx, int32_t pose, uint32_t* ranges,
                                   int64_t* n, hgsr_stream stream);
 
 /* Time the renderer on this input for tile sizes 8/16/32, the blend
- * schedules and (32 channels) both feature accumulations, then (up to 4 poses) the
+ * schedules and (32 and 64 channels) both feature accumulations, then (up to 4 poses) the
  * projection's grouping (1 Gaussian per thread, the default, suited to scenes
  * in spatial order -- hgsr_host_spatial_order --, or 4, often faster for
  * scenes in arbitrary order); keep the fastest as

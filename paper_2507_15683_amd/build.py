@@ -27,7 +27,8 @@ HOST_FLAGS = ["-O2", "-std=c++17", "-fPIC", "-Wall", "-I", os.path.join(HERE, ".
 # Matrix-core results written to ordinary VGPRs, where the epilogue reads them
 # (no accumulator-to-VGPR moves per tile).
 FILE_FLAGS = {"match.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
-              "backward.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
+              "backward.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
+              "blend.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 
 
 def build(verbose: bool = False) -> str:

@@ -24,17 +24,6 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef short shortx4 __attribute__((ext_vector_type(4)));
 
-// The blend backward's work split, at every tile size: a wave owns an 8x8
-// block of pixels, one per lane, and a workgroup owns a 16x16 block (tile 8:
-// 8x8).  A 32x32 tile is four workgroups that walk the same list, each over
-// one quadrant.
-template <int TILE>
-struct BwdShape {
-  static constexpr int kThreads = TILE == 8 ? 64 : 256;
-  static constexpr int kWaves = kThreads / kWave;
-  static constexpr int kParts = TILE == 32 ? 4 : 1;  // workgroups per tile
-};
-constexpr int kBwdBatch = 64;   // splats staged per round: a wave's hits are one 64-bit mask
 constexpr int kBwdGroup = 16;   // splats per matrix-core product
 constexpr int kBwdHalf = 8;     // splats per transposed reduction
 constexpr int kBwdRow = 68;     // words per LDS row of 64 pixels (16-byte reads of 8 rows hit 32 banks)
@@ -80,13 +69,6 @@ __device__ __forceinline__ void row_broadcast(float v, float out[4]) {
   out[1] = __uint_as_float(a[1]);
   out[2] = __uint_as_float(b[0]);
   out[3] = __uint_as_float(b[1]);
-}
-
-// Orders this wave's LDS writes before its LDS reads (and the reverse).
-__device__ __forceinline__ void wave_lds_fence() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // Sums eight per-lane values over the eight lane octets (lanes that agree in
@@ -168,8 +150,8 @@ __device__ __forceinline__ bool finite_bits(float v) { return (__float_as_uint(v
 // for).
 template <int TILE, int D, bool FEATGRAD, bool RES, bool PO>
 __device__ __forceinline__ void blend_bwd_item(const BackArgs& a, const int item) {
-  using Sh = BwdShape<TILE>;
-  constexpr int NT = Sh::kThreads, NW = Sh::kWaves, NB = kBwdBatch, ROW = kBwdRow;
+  using Sh = BlockShape<TILE>;
+  constexpr int NT = Sh::kThreads, NW = Sh::kWaves, NB = kListRound, ROW = kBwdRow;
   constexpr int DV = D / 8;                    // 16-byte bf16 vectors per feature
   constexpr int CG = D / 4;                    // channels per lane row of the matrix operands
   constexpr int CGA = CG > 0 ? CG : 1;
@@ -762,7 +744,7 @@ __device__ __forceinline__ void blend_bwd_item(const BackArgs& a, const int item
 // (PERSIST) a grid of workgroups claiming runs of kQueueChunk items from a
 // device counter until it passes the item count.
 template <int TILE, int D, bool FEATGRAD, bool RES, bool PERSIST, bool PO = false>
-__global__ __launch_bounds__(BwdShape<TILE>::kThreads, (PO && D <= 32 && !PERSIST && TILE != 8) ? 4 : 1) void
+__global__ __launch_bounds__(BlockShape<TILE>::kThreads, (PO && D <= 32 && !PERSIST && TILE != 8) ? 4 : 1) void
 blend_bwd_kernel(BackArgs a) {
   if constexpr (PERSIST) {
     if (a.flags[0] & 3) return;
@@ -806,7 +788,7 @@ void launch_loss_reduce(const float* part, int32_t tiles_per_pose, int32_t P, fl
 
 template <int TILE, int D, bool PERSIST>
 static void launch_bwd_tdp(const BackArgs& a, int n_ctas, hipStream_t s) {
-  constexpr int NT = BwdShape<TILE>::kThreads;
+  constexpr int NT = BlockShape<TILE>::kThreads;
   constexpr bool F = D > 0;  // without features there is no feature gradient
   if (a.res_rgb_t) {
     if (F && a.g_featvec)
@@ -839,8 +821,6 @@ static void launch_bwd_t(const BackArgs& a, hipStream_t s) {
     default: launch_bwd_td<TILE, 64>(a, s); break;
   }
 }
-
-int blend_bwd_parts(int tile) { return tile == 32 ? BwdShape<32>::kParts : 1; }
 
 void launch_blend_bwd(const BackArgs& a, hipStream_t s) {
   switch (a.c.tile) {

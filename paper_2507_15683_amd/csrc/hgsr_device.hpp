@@ -94,60 +94,6 @@ __device__ __forceinline__ float row_sum16(float v) {
   return v;
 }
 
-// Sums ten per-lane values over the wave and atomically adds total v to
-// dst[v] (dst in LDS or global memory).  A reduce-scatter: the lane-half
-// exchange (v_permlane32_swap) pairs value i with value 5 + i, so lanes 0-31
-// carry values 0-4 and lanes 32-63 values 5-9; the row exchange
-// (v_permlane16_swap) pairs them again, leaving three partial sums per lane
-// that a 16-lane DPP row sum completes.  Totals end in lanes 0, 16, 32, 48:
-// row r = lane / 16 holds values 5 (r / 2) + (r % 2), 5 (r / 2) + 2 + (r % 2)
-// and, for even rows, 5 (r / 2) + 4.
-__device__ __forceinline__ void wave_add10(const float g[10], float* dst) {
-  float b[5];
-#pragma unroll
-  for (int i = 0; i < 5; ++i) {
-    const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(g[i]), __float_as_uint(g[5 + i]), false, false);
-    b[i] = __uint_as_float(s[0]) + __uint_as_float(s[1]);
-  }
-  const auto s0 = __builtin_amdgcn_permlane16_swap(__float_as_uint(b[0]), __float_as_uint(b[1]), false, false);
-  const auto s1 = __builtin_amdgcn_permlane16_swap(__float_as_uint(b[2]), __float_as_uint(b[3]), false, false);
-  const auto s2 = __builtin_amdgcn_permlane16_swap(__float_as_uint(b[4]), __float_as_uint(b[4]), false, false);
-  const float c0 = row_sum16(__uint_as_float(s0[0]) + __uint_as_float(s0[1]));
-  const float c1 = row_sum16(__uint_as_float(s1[0]) + __uint_as_float(s1[1]));
-  const float c2 = row_sum16(__uint_as_float(s2[0]) + __uint_as_float(s2[1]));
-  const int lane = threadIdx.x & (kWave - 1);
-  if ((lane & 15) == 0) {
-    const int base = 5 * (lane >> 5), odd = (lane >> 4) & 1;
-    atomicAdd(dst + base + odd, c0);
-    atomicAdd(dst + base + 2 + odd, c1);
-    if (!odd) atomicAdd(dst + base + 4, c2);
-  }
-}
-
-// The same for eight of the ten sums (0-4 and 7-9; 5 and 6 are left alone):
-// each value meets the same reduction tree as in wave_add10 (lane pairs 32
-// apart, then 16 apart, then a row sum), so the eight results have the same
-// bits.
-__device__ __forceinline__ void wave_add8(const float g[10], float* dst) {
-  const float lo[4] = {g[0], g[1], g[2], g[3]}, hi[4] = {g[4], g[7], g[8], g[9]};
-  float b[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(lo[i]), __float_as_uint(hi[i]), false, false);
-    b[i] = __uint_as_float(s[0]) + __uint_as_float(s[1]);
-  }
-  const auto s0 = __builtin_amdgcn_permlane16_swap(__float_as_uint(b[0]), __float_as_uint(b[1]), false, false);
-  const auto s1 = __builtin_amdgcn_permlane16_swap(__float_as_uint(b[2]), __float_as_uint(b[3]), false, false);
-  const float c0 = row_sum16(__uint_as_float(s0[0]) + __uint_as_float(s0[1]));
-  const float c1 = row_sum16(__uint_as_float(s1[0]) + __uint_as_float(s1[1]));
-  const int lane = threadIdx.x & (kWave - 1);
-  if ((lane & 15) == 0) {
-    const int half = lane >> 5, odd = (lane >> 4) & 1;
-    atomicAdd(dst + (half ? (odd ? 7 : 4) : odd), c0);       // g0, g1 | g4, g7
-    atomicAdd(dst + (half ? (odd ? 9 : 8) : 2 + odd), c1);   // g2, g3 | g8, g9
-  }
-}
-
 // World covariance Sigma_w = R_q diag(exp(2 ls)) R_q^T, (w,x,y,z) quaternion
 // normalised here.  Returns xx, xy, xz, yy, yz, zz.
 __device__ __forceinline__ void cov3_from(const float4 q4, const float ls[3], float S[6]) {
@@ -372,6 +318,31 @@ __device__ __forceinline__ int wave_sort256(const uint64_t* keys, const uint32_t
     }
   }
   return R;
+}
+
+// The split of the blend, its backward and the visibility walk: a wave owns an
+// 8x8 block of pixels, one per lane, and a workgroup a 16x16 block (tile 8:
+// 8x8).  A 32x32 tile is four workgroups that walk the same list, each over one
+// quadrant.
+template <int TILE>
+struct BlockShape {
+  static constexpr int kThreads = TILE == 8 ? 64 : 256;
+  static constexpr int kWaves = kThreads / kWave;
+  static constexpr int kParts = TILE == 32 ? 4 : 1;  // workgroups per tile
+  static constexpr int kSide = TILE == 8 ? 8 : 16;   // pixels along a side of the workgroup's block
+};
+constexpr int kListRound = 64;  // splats staged per round: a wave's hits are one 64-bit mask
+
+// Orders this wave's LDS writes before its LDS reads (and the reverse).
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Whether either of two packed bfloat16 values is infinite or NaN.
+__device__ __forceinline__ bool nonfinite_bf16x2(uint32_t w) {
+  return (w & 0x7f80u) == 0x7f80u || (w & 0x7f800000u) == 0x7f800000u;
 }
 
 template <int TILE>

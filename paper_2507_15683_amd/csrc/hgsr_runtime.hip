@@ -252,7 +252,7 @@ hgsr_status for_each_render_buf(hgsr_ctx* c, int P, const CamArgs& cam, bool lsd
   TRY(f(c->finalT, npix * sizeof(float)));
   TRY(f(c->nused, npix * sizeof(uint32_t)));
   TRY(f(c->part_vis, std::max(P, 1) * sizeof(uint64_t)));
-  TRY(f(c->loss_part, ntile * blend_bwd_parts(cam.tile) * sizeof(float)));
+  TRY(f(c->loss_part, ntile * blend_parts(cam.tile) * sizeof(float)));
   if (lsd) {
     TRY(f(c->rec_keys, nrec * sizeof(uint32_t)));
     TRY(f(c->rec_offsets, nrec * sizeof(uint32_t)));
@@ -320,7 +320,7 @@ hgsr_status resolve(hgsr_ctx* c, const hgsr_gaussians* g, const float* poses, in
   r->lsd = opts->sort_mode == HGSR_SORT_LSD;
   const float near_z = opts->near_z > 0.f ? opts->near_z : 0.2f;
   r->cam = make_cam(*K, r->tile, near_z);
-  if (static_cast<int64_t>(P) * r->cam.tiles_per_pose >= (1ll << 31))
+  if (static_cast<int64_t>(P) * r->cam.tiles_per_pose * blend_parts(r->tile) >= (1ll << 31))
     return fail(HGSR_ERR_INVALID_ARG, "too many (pose, tile) items");
   return HGSR_OK;
 }
@@ -549,7 +549,7 @@ static hgsr_status render_impl(hgsr_ctx* c, const hgsr_gaussians* g, const float
   bl.list_gid = c->sorted_gid;
   {
     int fa = opts->feat_accum;
-    if (fa == HGSR_FEAT_AUTO) fa = c->tuned_feat ? c->tuned_feat : HGSR_FEAT_VALU;
+    if (fa == HGSR_FEAT_AUTO) fa = c->tuned_feat ? c->tuned_feat : HGSR_FEAT_MFMA;
     bl.feat_mfma = fa == HGSR_FEAT_MFMA ? 1 : 0;
   }
   bl.recs = c->recs.as<Splat>();
@@ -562,11 +562,11 @@ static hgsr_status render_impl(hgsr_ctx* c, const hgsr_gaussians* g, const float
   bl.final_T = c->finalT.as<float>();
   bl.n_used = c->nused.as<uint32_t>();
   bl.schedule = sched;
-  bl.n_items = static_cast<int32_t>(ntile);
+  bl.n_items = static_cast<int32_t>(ntile) * blend_parts(tile);
   bl.queue = reinterpret_cast<uint32_t*>(misc + kQueue);
   bl.flags = misc + kFlags;
-  int n_ctas = static_cast<int>(ntile);
-  if (sched != HGSR_SCHED_GRID) n_ctas = static_cast<int>(std::min<int64_t>(ntile, persistent_ctas(c, tile)));
+  int n_ctas = bl.n_items;
+  if (sched != HGSR_SCHED_GRID) n_ctas = static_cast<int>(std::min<int64_t>(bl.n_items, persistent_ctas(c, tile)));
   launch_blend_fwd(bl, g->feat_dim, opts->feat_out_bf16 != 0, n_ctas, s);
   HIP_TRY(hipGetLastError());
   hipEvent_t e3 = stamp(c, s);
@@ -1248,7 +1248,7 @@ static hgsr_status backward_impl(hgsr_ctx* c, const hgsr_grad_outputs* go, const
   b.pose_only = rt && !gr->opacities ? 1 : 0;
   b.schedule = c->opts.schedule;
   b.share_target = b.schedule == HGSR_SCHED_GRID && rt && rt->shared_target && P > 1 ? 1 : 0;
-  const int parts = blend_bwd_parts(c->cam.tile);
+  const int parts = blend_parts(c->cam.tile);
   b.n_items = P * c->cam.tiles_per_pose * parts;
   b.n_ctas = static_cast<int32_t>(std::min<int64_t>(b.n_items, persistent_ctas(c, c->cam.tile)));
   b.queue = reinterpret_cast<uint32_t*>(misc + kQueueBwd);
@@ -1416,7 +1416,7 @@ hgsr_status hgsr_autotune(hgsr_ctx* c, const hgsr_gaussians* g, const float* pos
     for (int sc : scheds)
       for (int fa : feats) {
       if (P == 1 && sc == HGSR_SCHED_TILE_MAJOR) continue;
-      if (fa == HGSR_FEAT_MFMA && (g->feat_dim != 32 || t == 32)) continue;
+      if (fa == HGSR_FEAT_MFMA && g->feat_dim != 32 && g->feat_dim != 64) continue;
       hgsr_opts o = *opts;
       o.tile = t;
       o.schedule = sc;

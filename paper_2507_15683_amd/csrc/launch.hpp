@@ -80,7 +80,7 @@ struct BlendArgs {
   const uint2* ranges;
   const uint32_t* list;      // per-tile record indices in (depth, index) order
   const uint32_t* list_gid;  // Gaussian index of each list entry
-  int32_t feat_mfma;         // accumulate 32 feature channels on the matrix cores
+  int32_t feat_mfma;         // sum 32 or 64 feature channels on the matrix cores
   const Splat* recs;
   const uint16_t* feat;      // n x D bf16
   float bg[3];
@@ -91,7 +91,7 @@ struct BlendArgs {
   float* final_T;
   uint32_t* n_used;
   int32_t schedule;
-  int32_t n_items;
+  int32_t n_items;           // (pose, tile) times blend_parts(tile)
   uint32_t* queue;
   const int32_t* flags;
 };
@@ -111,7 +111,7 @@ struct BackArgs {
   int32_t pose_only;
   int32_t schedule;          // kSchedGrid, or a persistent queue of (pose, tile) items
   int32_t share_target;      // grid schedule, one residual target for all poses: poses interleaved by tile runs
-  int32_t n_items;           // workgroups' items: (pose, tile) times blend_bwd_parts(tile)
+  int32_t n_items;           // workgroups' items: (pose, tile) times blend_parts(tile)
   int32_t n_ctas;            // workgroups of the persistent launch
   uint32_t* queue;           // item counter (zero before the launch)
   const float* fwd_depth;
@@ -243,10 +243,12 @@ void launch_ranges_from_sorted(const uint64_t* keys, const uint32_t* total, uint
 void launch_loss_reduce(const float* part, int32_t tiles_per_pose, int32_t P, float* loss, hipStream_t s);
 // probe.hip: wave64 FP32 FMA instructions per second the device issues
 hipError_t probe_valu_rate(int n_cu, hipStream_t s, double* wave_fma_per_s);
+// workgroups (items) per (pose, tile) of the blend, its backward (with a loss
+// share each) and the visibility walk
+int blend_parts(int tile);
 void launch_blend_fwd(const BlendArgs& a, int D, bool bf16_out, int n_ctas, hipStream_t s);
 
 // backward.hip
-int blend_bwd_parts(int tile);  // workgroups (and loss shares) per (pose, tile)
 void launch_blend_bwd(const BackArgs& a, hipStream_t s);
 void launch_project_bwd(const ProjBackArgs& a, hipStream_t s);
 void launch_zero_grad_rec(float* g, const uint32_t* pose_count, uint32_t rec_cap, int P, hipStream_t s);

@@ -172,6 +172,45 @@ def test_mfma_feature_accumulation(hg, oracle_mod, tile):
         parity(mf, ref, p=p, label=f"mfma/t{tile}/{p}", max_fragile_frac=0.05)
 
 
+@pytest.mark.parametrize("tile", [8, 16, 32])
+@pytest.mark.parametrize("D", [0, 8, 16, 32, 64])
+def test_long_lists_at_every_feature_width(hg, oracle_mod, D, tile):
+    """Lists of several staging rounds (64 to 256 splats) with ragged ends:
+    the oracle's bar, and the matrix-core and FMA feature sums agree but for
+    the order of the sum."""
+    sc, P, cam = synth.tiny_scene(4000, 57 + D, width=45, height=37, feat_dim=D, sh_degree=1)
+    sc = sc.copy()
+    sc.opacities[:] *= 0.15  # long walks: many splats blend before a pixel stops
+    log(f"case: long lists D={D} tile={tile}")
+    out, r = _render(hg, sc, P, cam, tile=tile)
+    log("longest list", r.stats()["max_tile_list"])
+    assert r.stats()["max_tile_list"] > (130 if tile == 8 else 260)
+    ref = oracle_mod.render(sc, P[0], cam, tile=16, margin=1)
+    parity(out, ref, label=f"long/d{D}/t{tile}", max_fragile_frac=0.2)
+    if D:
+        va, _ = _render(hg, sc, P, cam, tile=tile, feat_accum="valu")
+        assert np.array_equal(to_np(out["rgb"]), to_np(va["rgb"]))
+        assert np.abs(to_np(out["feat"]) - to_np(va["feat"])).max() < 1e-5
+
+
+@pytest.mark.parametrize("D", [16, 32, 64])
+def test_non_finite_features_stay_with_their_splat(hg, D):
+    """An infinite feature of one splat makes exactly the pixels that blend
+    the splat non-finite, in its channel."""
+    sc, P, cam = synth.tiny_scene(400, 91, width=53, height=45, feat_dim=D, sh_degree=0)
+    sc = sc.copy()
+    feat, gid, ch = sc.feat.copy(), 211, D - 3
+    log(f"case: non-finite feature D={D}")
+    sc.feat[:] = 0
+    sc.feat[gid, ch] = 0x3F80  # 1.0
+    blends = to_np(_render(hg, sc, P, cam)[0]["feat"]) != 0
+    assert blends.any() and not blends.all()
+    sc.feat[:] = feat
+    sc.feat[gid, ch] = 0x7F80  # +infinity
+    got = to_np(_render(hg, sc, P, cam)[0]["feat"])
+    assert np.array_equal(~np.isfinite(got), blends)
+
+
 def test_batched_equals_single(hg):
     sc, P, cam = synth.tiny_scene(400, 8, width=80, height=64, feat_dim=8, sh_degree=2)
     Ps = synth.perturb_poses(P[0], 7, 4, 1.5, 3.0)
