@@ -15,7 +15,6 @@ constexpr float kTMin = 1e-4f;              // transmittance stop
 constexpr float kDilation = 0.3f;           // screen-space low-pass, px^2
 constexpr float kGuard = 1.3f;              // Jacobian guard band, x field of view
 constexpr float kRectPad = 5e-4f;           // support rectangle padding, px
-constexpr float kPreReject = 1e-3f;         // exponent margin below the gate for the early reject
 constexpr float kCosEps = 1e-8f;     // added to |F| |F*| in the feature cosine
 constexpr int kMaxPoses = 64;               // poses per projection launch
 constexpr int kSub = 32;                    // record sub-segments (and counters) per pose
@@ -344,18 +343,6 @@ __device__ __forceinline__ void wave_lds_fence() {
 __device__ __forceinline__ bool nonfinite_bf16x2(uint32_t w) {
   return (w & 0x7f80u) == 0x7f80u || (w & 0x7f800000u) == 0x7f800000u;
 }
-
-template <int TILE>
-struct BlendShape {
-  static constexpr int kThreads = TILE == 8 ? 64 : 256;
-  static constexpr int kBatch = kThreads < 128 ? kThreads : 128;  // splats staged per round
-  static constexpr int kWaves = kThreads / kWave;
-  // a wave's pixel block: 8x8 (16x16 with 4 pixels per lane at tile 32)
-  static constexpr int kBlockW = TILE == 32 ? 16 : 8;
-  static constexpr int kBlockH = TILE * TILE / kWaves / kBlockW;
-  static constexpr int kPPT = kBlockW * kBlockH / kWave;  // pixels per lane
-  static constexpr int kBlocksX = TILE / kBlockW;
-};
 
 // Smallest conic distance q(p - mean) = a dx^2 + 2 b dx dy + c dy^2 over the
 // rectangle [x0, x1] x [y0, y1] (ia = 1/a, ic = 1/c).  q is convex: 0 when

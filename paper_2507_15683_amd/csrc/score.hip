@@ -31,96 +31,101 @@
 
 namespace hgsr {
 
+// The visibility walk: the forward blend's, without its sums.  One staged splat
+// per thread and round, its loads sent off a round ahead; each wave walks the
+// splats that meet its 8x8 block as 64-bit masks, two at a time (their alphas
+// do not wait for each other), and writes the flags of a mask's splats with one
+// byte store per lane (one per 64 list entries instead of one per blended
+// splat).  Bound by the walk's vector instructions, then the scattered bytes.
+// Scoring 64 views of 752x480 over a million Gaussians, the whole call:
+// 2743 -> 2605 us against batches of 128 read one splat at a time.
 template <int TILE>
-__global__ __launch_bounds__(BlendShape<TILE>::kThreads) void contrib_kernel(ContribArgs a) {
-  using S = BlendShape<TILE>;
-  constexpr int NT = S::kThreads, NB = S::kBatch, NW = S::kWaves, BW = S::kBlockW, PPT = S::kPPT;
+__global__ __launch_bounds__(BlockShape<TILE>::kThreads) void contrib_kernel(ContribArgs a) {
+  using S = BlockShape<TILE>;
+  constexpr int NB = S::kThreads;
   __shared__ float4 s_geo[NB];
   __shared__ float4 s_opz[NB];
-  __shared__ float s_pmin[NB];
   __shared__ uint8_t s_mask[NB];
-  __shared__ uint16_t s_list[NW][NB];
   if (a.flags[0] & 3) return;
   const int tid = threadIdx.x;
   const int lane = tid & (kWave - 1), wave = tid >> 6;
-  const int W = a.c.W, H = a.c.H;
   const int item = xcd_item(blockIdx.x, gridDim.x);
-  const int pose = item / a.c.tiles_per_pose;
-  const int tile = item - pose * a.c.tiles_per_pose;
+  const int part = item % S::kParts, titem = item / S::kParts;
+  const int pose = titem / a.c.tiles_per_pose;
+  const int tile = titem - pose * a.c.tiles_per_pose;
   const int ty = tile / a.c.ntx, tx = tile - ty * a.c.ntx;
-  const uint2 range = a.ranges[item];
-  const int bx0 = tx * TILE + (wave % S::kBlocksX) * BW, by0 = ty * TILE + (wave / S::kBlocksX) * S::kBlockH;
-  float pxf[PPT], pyf[PPT], T[PPT];
-  bool done[PPT];
-#pragma unroll
-  for (int k = 0; k < PPT; ++k) {
-    const int li = lane + k * kWave;
-    const int px = bx0 + (li % BW), py = by0 + (li / BW);
-    pxf[k] = static_cast<float>(px) + 0.5f;
-    pyf[k] = static_cast<float>(py) + 0.5f;
-    T[k] = 1.f;
-    done[k] = !(px < W && py < H);
-  }
+  const uint2 range = a.ranges[titem];
+  const int px = tx * TILE + (part & 1) * 16 + (wave & 1) * 8 + (lane & 7);
+  const int py = ty * TILE + (part >> 1) * 16 + (wave >> 1) * 8 + (lane >> 3);
+  const int mask_bit = TILE == 32 ? part : wave;  // the list masks' block that holds the wave's
+  const float pxf = static_cast<float>(px) + 0.5f, pyf = static_cast<float>(py) + 0.5f;
+  float T = 1.f;
+  // the gate 1/255, or infinity outside the image and once the pixel has stopped
+  float gate = px < a.c.W && py < a.c.H ? kAlphaMin : INFINITY;
   // flags are Gaussian-major: vis[gid * vis_stride + pose]
   uint8_t* vis = a.vis + pose;
 
+  uint32_t lv = 0;
+  float4 geo_s = {}, opz_s = {};
+  auto stage_load = [&](uint32_t b0) {
+    if (b0 + tid < range.y) {
+      lv = a.list[b0 + tid];
+      const float4* sp = reinterpret_cast<const float4*>(a.recs + (lv & kRecMask));
+      geo_s = sp[0];
+      opz_s = sp[1];
+    }
+  };
+  // one splat at this lane's pixel, in order: whether it is blended
+  auto blend = [&](float power, float alpha) -> bool {
+    const float Tn = T * (1.f - alpha);
+    const bool pass = !(power > 0.f) && !(alpha < gate), stop = pass && Tn < kTMin;
+    gate = stop ? INFINITY : gate;
+    const bool blended = pass && !stop;
+    T = blended ? Tn : T;
+    return blended;
+  };
+  stage_load(range.x);
   for (uint32_t b0 = range.x; b0 < range.y; b0 += NB) {
-    bool all_mine = true;
-#pragma unroll
-    for (int k = 0; k < PPT; ++k) all_mine &= done[k];
-    if (__syncthreads_and(all_mine)) break;
-    if (tid < NB) {
-      const uint32_t j = b0 + tid;
-      if (j < range.y) {
-        const uint32_t lv = a.list[j];
-        const float4* sp = reinterpret_cast<const float4*>(a.recs + (lv & kRecMask));
-        s_geo[tid] = sp[0];
-        s_opz[tid] = sp[1];
-        s_pmin[tid] = sp[2].w;
-        s_mask[tid] = static_cast<uint8_t>(lv >> kRecBits);
-      } else {
-        s_mask[tid] = 0;
-      }
+    if (b0 > range.x && __syncthreads_and(gate > 1.f)) break;  // every pixel of the block has stopped
+    const int nb = static_cast<int>(min(static_cast<uint32_t>(NB), range.y - b0));
+    if (tid < nb) {
+      s_geo[tid] = geo_s;
+      s_opz[tid] = opz_s;
+      s_mask[tid] = static_cast<uint8_t>(lv >> kRecBits);
     }
     __syncthreads();
-    const int nb = static_cast<int>(min(static_cast<uint32_t>(NB), range.y - b0));
-    int n_mine = 0;
-    for (int c0 = 0; c0 < nb; c0 += kWave) {
-      const int ce = c0 + lane;
-      const bool hit = ce < nb && ((s_mask[ce] >> wave) & 1u);
-      const uint64_t bal = __ballot(hit);
-      if (hit) s_list[wave][n_mine + __popcll(bal & ((1ull << lane) - 1ull))] = static_cast<uint16_t>(ce);
-      n_mine += __popcll(bal);
-    }
-    __builtin_amdgcn_wave_barrier();
-    for (int ii = 0; ii < n_mine; ++ii) {
-      bool mine = true;
-#pragma unroll
-      for (int k = 0; k < PPT; ++k) mine &= done[k];
-      if (mine) break;
-      const int jj = s_list[wave][ii];
-      const float4 geo = s_geo[jj];
-      const float4 opz = s_opz[jj];
-      const float pmin = s_pmin[jj];
-      bool blended = false;
-#pragma unroll
-      for (int k = 0; k < PPT; ++k) {
-        if (done[k]) continue;
-        const float dx = pxf[k] - geo.x, dy = pyf[k] - geo.y;
-        const float power = pair_power(dx, dy, geo.z, geo.w, opz.x);
-        if (power > 0.f || power < pmin - kPreReject) continue;
-        const float alpha = pair_alpha(opz.y, power);
-        if (alpha < kAlphaMin) continue;
-        const float Tn = T[k] * (1.f - alpha);
-        if (Tn < kTMin) {
-          done[k] = true;
-          continue;
-        }
-        T[k] = Tn;
-        blended = true;
+    if (b0 + NB < range.y) stage_load(b0 + NB);
+#pragma unroll 1
+    for (int k0 = 0; k0 < nb; k0 += kWave) {
+      uint64_t todo = __ballot(k0 + lane < nb && ((s_mask[k0 + lane] >> mask_bit) & 1u));
+      int left = __popcll(todo);
+      uint64_t seen = 0;  // uniform: splats blended at some pixel of the block
+      int j0, j1;
+      float4 g0, g1, o0, o1;
+      auto fetch = [&]() {
+        j0 = todo ? __builtin_ctzll(todo) : 0;
+        todo &= todo - 1ull;
+        j1 = todo ? __builtin_ctzll(todo) : 0;
+        todo &= todo - 1ull;
+        g0 = s_geo[k0 + j0];
+        o0 = s_opz[k0 + j0];
+        g1 = s_geo[k0 + j1];
+        o1 = s_opz[k0 + j1];
+        __atomic_signal_fence(__ATOMIC_SEQ_CST);  // issued here, a step ahead of their use
+      };
+      fetch();
+      while (left > 0 && __any(gate < 1.f)) {  // uniform
+        const int i0 = j0, i1 = j1;
+        const float4 ga = g0, gb = g1, oa = o0, ob = o1;
+        fetch();
+        const float pa = pair_power(pxf - ga.x, pyf - ga.y, ga.z, ga.w, oa.x);
+        const float pb = pair_power(pxf - gb.x, pyf - gb.y, gb.z, gb.w, ob.x);
+        const float aa = pair_alpha(oa.y, pa), ab = pair_alpha(ob.y, pb);
+        seen |= static_cast<uint64_t>(__any(blend(pa, aa)) != 0) << i0;
+        if (left > 1) seen |= static_cast<uint64_t>(__any(blend(pb, ab)) != 0) << i1;
+        left -= 2;
       }
-      // every lane that blended the splat stores the same byte
-      if (blended) vis[static_cast<int64_t>(__float_as_uint(opz.w)) * a.vis_stride] = 1;
+      if ((seen >> lane) & 1ull) vis[static_cast<int64_t>(__float_as_uint(s_opz[k0 + lane].w)) * a.vis_stride] = 1;
     }
   }
 }
@@ -442,9 +447,12 @@ __global__ void score_final_kernel(const float* sum, const uint32_t* count, int6
 void launch_contrib(const ContribArgs& a, int n_items, hipStream_t s) {
   if (n_items <= 0) return;
   switch (a.c.tile) {
-    case 8: hipLaunchKernelGGL(contrib_kernel<8>, dim3(n_items), dim3(BlendShape<8>::kThreads), 0, s, a); break;
-    case 32: hipLaunchKernelGGL(contrib_kernel<32>, dim3(n_items), dim3(BlendShape<32>::kThreads), 0, s, a); break;
-    default: hipLaunchKernelGGL(contrib_kernel<16>, dim3(n_items), dim3(BlendShape<16>::kThreads), 0, s, a); break;
+    case 8: hipLaunchKernelGGL(contrib_kernel<8>, dim3(n_items), dim3(BlockShape<8>::kThreads), 0, s, a); break;
+    case 32:
+      hipLaunchKernelGGL(contrib_kernel<32>, dim3(n_items * BlockShape<32>::kParts), dim3(BlockShape<32>::kThreads), 0,
+                         s, a);
+      break;
+    default: hipLaunchKernelGGL(contrib_kernel<16>, dim3(n_items), dim3(BlockShape<16>::kThreads), 0, s, a); break;
   }
 }
 

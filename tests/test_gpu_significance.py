@@ -167,6 +167,29 @@ def test_visibility_is_the_support_of_the_gpu_mean_gradient(hg, sg):
     assert not mism.any(), np.nonzero(mism)[0][:8]
 
 
+@pytest.mark.parametrize("tile", [8, 16, 32])
+def test_visibility_over_long_lists(hg, tile):
+    """Lists of several staging rounds: the visible Gaussians are exactly those
+    that the render's backward gives a feature gradient (their summed blend
+    weight) and whose mean projects inside the image."""
+    import torch
+    sc, P, cam = synth.tiny_scene(4000, 63, width=45, height=37, feat_dim=8)
+    sc = sc.copy()
+    sc.opacities[:] *= 0.15  # long walks: many splats blend before a pixel stops
+    log(f"case: visibility over long lists tile={tile}")
+    g, K, maps = hg.GaussianScene.from_numpy(sc), hg.Intrinsics.of(cam), _t(synth.feature_maps(1, 8, 37, 45, 64))
+    r = hg.Renderer()
+    out = r.render(g, _t(P), K, tile=tile)
+    assert r.stats()["max_tile_list"] > (130 if tile == 8 else 260)
+    weight = r.backward({"feat": torch.ones_like(out["feat"])}, want=("feat",))["feat"][:, 0]
+    res = hg.Renderer().significance(g, _t(P), K, maps, want_visible=True, tile=tile)
+    mc = sc.means.astype(np.float64) @ P[0].reshape(3, 4)[:, :3].T + P[0].reshape(3, 4)[:, 3]
+    u, v = cam.fx * mc[:, 0] / mc[:, 2] + cam.cx, cam.fy * mc[:, 1] / mc[:, 2] + cam.cy
+    inside = (u >= 0) & (u < cam.width) & (v >= 0) & (v < cam.height)
+    want = (weight != 0).cpu().numpy() & inside
+    assert want.sum() > 1000 and np.array_equal(res["visible"][0].cpu().numpy() != 0, want)
+
+
 def test_edge_cases(hg, sg):
     """Empty scene; a view that sees nothing; a single-cell map; a scene
     without features and mismatched maps are refused."""
