@@ -48,8 +48,9 @@ constexpr int kFeatRound = 4;  // 16-byte feature reads per round of the FMA for
 // the order of the FP32 sum differs from one FMA per splat and channel.  The
 // FMA form spends 32 of 70 VALU instructions and 8 of 11 LDS reads per splat
 // on the features (both units near their limits); this one about 7 and 1.
-// A splat with a non-finite feature is summed apart, at the pixels that blend
-// it (a zero weight times infinity would reach the others).
+// A piece of eight channels that holds a non-finite value enters the product as
+// zeros and is summed apart, at the pixels that blend its splat (a zero weight
+// times infinity would reach the others).
 template <int TILE, int D, bool BF16, bool MF, bool PERSIST>
 __global__ __launch_bounds__(BlockShape<TILE>::kThreads, 1) void blend_fwd_kernel(BlendArgs a) {
   using S = BlockShape<TILE>;
@@ -171,9 +172,7 @@ __global__ __launch_bounds__(BlockShape<TILE>::kThreads, 1) void blend_fwd_kerne
               dst[1] = make_uint4(f.z << 16, f.z & 0xffff0000u, f.w << 16, f.w & 0xffff0000u);
             } else {
               if constexpr (MF) {
-                const bool odd = nonfinite_bf16x2(f.x) || nonfinite_bf16x2(f.y) || nonfinite_bf16x2(f.z) ||
-                                 nonfinite_bf16x2(f.w);
-                if (odd) {
+                if (nonfinite_bf16x8(f)) {
                   atomicOr(&s_odd[st_e >> 5], 1u << (st_e & 31));
                   f = make_uint4(0u, 0u, 0u, 0u);
                 }
@@ -372,17 +371,26 @@ __global__ __launch_bounds__(BlockShape<TILE>::kThreads, 1) void blend_fwd_kerne
               const int jj = __builtin_ctzll(odd_g);
               odd_g &= odd_g - 1ull;
               const int q = __popcll(rest0 & ((1ull << jj) - 1ull));
-              const uint16_t* f = a.feat + static_cast<int64_t>(__float_as_uint(s_sp[k0 + jj][1].w)) * D;
+              // the pieces of eight channels that were staged as zeros; the
+              // others of this splat are in the products above
+              const uint4* f = reinterpret_cast<const uint4*>(a.feat) +
+                               static_cast<int64_t>(__float_as_uint(s_sp[k0 + jj][1].w)) * DV;
 #pragma unroll
-              for (int side = 0; side < 2; ++side) {
-                const float wq = s_wt[wave][q][(lane & 31) + 32 * side];
-                if (wq == 0.f) continue;
+              for (int v = 0; v < DV; ++v) {
+                const uint4 x = f[v];
+                if (!nonfinite_bf16x8(x)) continue;  // uniform
+                const uint32_t x0 = lane < 32 ? x.x : x.z, x1 = lane < 32 ? x.y : x.w;
+                const float c[4] = {bf16_lo(x0), bf16_hi(x0), bf16_lo(x1), bf16_hi(x1)};
 #pragma unroll
-                for (int n = 0; n < NA; ++n)
+                for (int side = 0; side < 2; ++side) {
+                  const float wq = s_wt[wave][q][(lane & 31) + 32 * side];
+                  if (wq == 0.f) continue;
 #pragma unroll
-                  for (int k = 0; k < 16; ++k)
-                    acc[n][side][k] =
-                        fmaf(wq, bf16_lo(f[32 * n + 8 * (k / 4) + 4 * (lane >> 5) + (k % 4)]), acc[n][side][k]);
+                  for (int k = 0; k < 4; ++k) {
+                    const int i = 4 * (v % 4) + k;
+                    acc[v / 4][side][i] = fmaf(wq, c[k], acc[v / 4][side][i]);
+                  }
+                }
               }
             }
           }

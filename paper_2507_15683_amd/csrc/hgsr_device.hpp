@@ -344,6 +344,11 @@ __device__ __forceinline__ bool nonfinite_bf16x2(uint32_t w) {
   return (w & 0x7f80u) == 0x7f80u || (w & 0x7f800000u) == 0x7f800000u;
 }
 
+// Whether any of eight packed bfloat16 values is.
+__device__ __forceinline__ bool nonfinite_bf16x8(const uint4& f) {
+  return nonfinite_bf16x2(f.x) || nonfinite_bf16x2(f.y) || nonfinite_bf16x2(f.z) || nonfinite_bf16x2(f.w);
+}
+
 // Smallest conic distance q(p - mean) = a dx^2 + 2 b dx dy + c dy^2 over the
 // rectangle [x0, x1] x [y0, y1] (ia = 1/a, ic = 1/c).  q is convex: 0 when
 // the mean is inside, otherwise the smallest of the four edge minima, each a

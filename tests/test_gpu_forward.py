@@ -211,6 +211,33 @@ def test_non_finite_features_stay_with_their_splat(hg, D):
     assert np.array_equal(~np.isfinite(got), blends)
 
 
+@pytest.mark.parametrize("tile", [8, 16, 32])
+@pytest.mark.parametrize("D", [32, 64])
+def test_finite_channels_beside_a_non_finite_feature(hg, D, tile):
+    """One infinite or NaN feature of a splat, in each staged piece of eight
+    channels in turn: every other channel of the matrix-core sum is the FMA
+    sum but for rounding.  Both add at most n terms of magnitude w |f| with
+    sum of w at most 1, so each is within n 2^-24 max|f| of the exact value,
+    n the longest list."""
+    sc, P, cam = synth.tiny_scene(400, 92, width=53, height=45, feat_dim=D, sh_degree=0)
+    sc = sc.copy()
+    feat, gid = sc.feat.copy(), 211
+    fmax = np.abs((feat.astype(np.uint32) << 16).view(np.float32)).max()
+    for piece in range(D // 8):
+        for bits, k in ((0x7F80, 1), (0x7FC0, 6)):  # +infinity, NaN
+            log(f"case: non-finite feature D={D} tile={tile} piece {piece} bits {bits:#x}")
+            sc.feat[:] = feat
+            sc.feat[gid, 8 * piece + k] = bits
+            mf, r = _render(hg, sc, P, cam, tile=tile, feat_accum="mfma")
+            va, _ = _render(hg, sc, P, cam, tile=tile, feat_accum="valu")
+            a, b = to_np(mf["feat"]), to_np(va["feat"])
+            ok = np.isfinite(b)
+            assert np.array_equal(np.isfinite(a), ok)
+            assert ok[:, [c for c in range(D) if c != 8 * piece + k]].all() and not ok[:, 8 * piece + k].all()
+            tol = 2 * r.stats()["max_tile_list"] * 2.0 ** -24 * fmax
+            assert np.abs(a[ok] - b[ok]).max() <= tol
+
+
 def test_batched_equals_single(hg):
     sc, P, cam = synth.tiny_scene(400, 8, width=80, height=64, feat_dim=8, sh_degree=2)
     Ps = synth.perturb_poses(P[0], 7, 4, 1.5, 3.0)
