@@ -32,6 +32,25 @@ def _ptr(t: Optional[torch.Tensor]):
     return None if t is None else ctypes.c_void_p(t.data_ptr())
 
 
+def _outputs(out: dict, px: int, feat_dim: int, bf16: bool) -> _lib.Outputs:
+    """The library's view of a dict of output buffers for px pixels.  The kernels
+    store without bounds, so a buffer with fewer bytes than they write (FP32
+    features in a bfloat16 buffer among them) is refused here."""
+    for name, per_px in (("rgb", 12), ("depth", 4), ("alpha", 4), ("feat", (2 if bf16 else 4) * feat_dim)):
+        t = out[name]
+        if t is None or (t.is_contiguous() and t.numel() * t.element_size() >= px * per_px):
+            continue
+        have = t.untyped_storage().nbytes() - t.storage_offset() * t.element_size()
+        if have < px * per_px:
+            raise ValueError(f"{name}: the output buffer holds {have} bytes, the render writes {px * per_px}")
+    return _lib.Outputs(_ptr(out["rgb"]), _ptr(out["depth"]), _ptr(out["alpha"]), _ptr(out["feat"]))
+
+
+def _feat_bf16(out: dict, feat_bf16: bool) -> bool:
+    """Whether features are stored as bfloat16: a bfloat16 buffer takes nothing else."""
+    return feat_bf16 or (out["feat"] is not None and out["feat"].dtype == torch.bfloat16)
+
+
 @dataclasses.dataclass
 class Intrinsics:
     fx: float
@@ -329,7 +348,7 @@ class Renderer:
             raise ValueError("poses must be a contiguous float32 (P, 12) device tensor")
         P = poses.shape[0]
         g = scene.c()
-        o = _lib.Outputs(_ptr(out["rgb"]), _ptr(out["depth"]), _ptr(out["alpha"]), _ptr(out["feat"]))
+        o = _outputs(out, P * K.height * K.width, scene.feat_dim, bool(opts.feat_out_bf16))
         kc = K.c()
         self._keep = (scene, poses, out)
         check(self.lib.hgsr_render(self.ctx, ctypes.byref(g), _ptr(poses), P, ctypes.byref(kc), ctypes.byref(opts),
@@ -345,12 +364,15 @@ class Renderer:
                out=None, check_overflow=True, stream=None) -> dict:
         """Render P poses; returns dict(rgb (P,3,H,W), depth (P,H,W), alpha
         (P,H,W), feat (P,D,H,W) or None).  With check_overflow the call
-        synchronises, and re-renders after growing the workspace if needed."""
+        synchronises, and re-renders after growing the workspace if needed.
+        `out` may supply the buffers; a bfloat16 feature buffer is filled with
+        bfloat16 values whatever feat_bf16 says (FP32 ones would not fit)."""
         if poses.dim() == 1:
             poses = poses[None]
         P = poses.shape[0]
         if out is None:
             out = self.alloc_outputs(scene, P, K, feat_bf16)
+        feat_bf16 = _feat_bf16(out, feat_bf16)
         opts = self.opts(tile, sort, schedule, bg, near, feat_bf16, lds_sort_cap, feat_accum)
         for _ in range(6):
             self.render_into(scene, poses, K, out, opts, stream)
@@ -572,8 +594,9 @@ class Renderer:
         feat_accum="auto"."""
         g = scene.c()
         kc = K.c()
+        feat_bf16 = _feat_bf16(out, feat_bf16)
         opts = self.opts(16, sort, "grid", feat_bf16=feat_bf16)
-        o = _lib.Outputs(_ptr(out["rgb"]), _ptr(out["depth"]), _ptr(out["alpha"]), _ptr(out["feat"]))
+        o = _outputs(out, poses.shape[0] * K.height * K.width, scene.feat_dim, feat_bf16)
         res = _lib.TuneResult()
         check(self.lib.hgsr_autotune(self.ctx, ctypes.byref(g), _ptr(poses), poses.shape[0], ctypes.byref(kc),
                                      ctypes.byref(opts), ctypes.byref(o), int(with_backward),

@@ -238,6 +238,22 @@ def test_finite_channels_beside_a_non_finite_feature(hg, D, tile):
             assert np.abs(a[ok] - b[ok]).max() <= tol
 
 
+@pytest.mark.parametrize("D", [16, 32])
+def test_supplied_bfloat16_buffers(hg, D):
+    """A render into supplied buffers with a bfloat16 feature map gives what a
+    render with feat_bf16 gives, with and without the flag."""
+    import torch
+    sc, P, cam = synth.tiny_scene(300, 93, width=53, height=45, feat_dim=D, sh_degree=1)
+    log(f"case: supplied bfloat16 buffers D={D}")
+    ref, r = _render(hg, sc, P, cam, feat_bf16=True)
+    for kw in (dict(), dict(feat_bf16=True)):
+        out = r.alloc_outputs(hg.GaussianScene.from_numpy(sc), 1, hg.Intrinsics.of(cam), True)
+        got, _ = _render(hg, sc, P, cam, out=out, **kw)
+        assert got is out
+        for k in ("rgb", "depth", "alpha", "feat"):
+            assert torch.equal(got[k], ref[k]), k
+
+
 def test_batched_equals_single(hg):
     sc, P, cam = synth.tiny_scene(400, 8, width=80, height=64, feat_dim=8, sh_degree=2)
     Ps = synth.perturb_poses(P[0], 7, 4, 1.5, 3.0)
