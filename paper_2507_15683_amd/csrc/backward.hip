@@ -114,10 +114,13 @@ __device__ __forceinline__ bool finite_bits(float v) { return (__float_as_uint(v
 // numbers per splat to LDS, dL/dpower d and the blend weight w, and after eight
 // splats the wave reads them back transposed -- a lane takes one splat's row of
 // eight pixels -- and forms the sums of d, d dx, d dx^2 and w g there, every
-// lane busy, with one cross-lane step per eight splats.  The sums kept per
-// record are the moments (sum d dx, d dy, d dx^2, d dx dy, d dy^2, d, w gZ,
-// w gC); the projection backward turns them into conic, mean and opacity
-// gradients.  The waves keep their sums apart in LDS until the flush: float
+// lane busy, with one cross-lane step per eight splats.  With the conic
+// (a, b, c) the sums kept per record are d (a dx + b dy) and d (b dx + c dy),
+// the mean's gradient, the moments d dx^2, d dx dy, d dy^2, d, and w gZ, w gC;
+// the projection backward turns the moments into conic and opacity gradients.
+// The mean's two sums are formed per pixel: along a needle a dx and b dy cancel
+// there, and sums of d dx and d dy combined at the end miss the 64-bit value by
+// up to 48 x 2^-24 of the terms (needles of 60 px), these by less than 0.1.  The waves keep their sums apart in LDS until the flush: float
 // atomics there take about a cycle per lane (300 of 3,700 us at 64 poses).
 //
 // The feature part of h_j = gF . f_j is, for 16 splats and 64 pixels, a matrix
@@ -496,7 +499,10 @@ __device__ __forceinline__ void blend_bwd_item(const BackArgs& a, const int item
   const uint32_t n_max = s_max;
   if (n_max == 0) return;
 
-  float S = gT * Tf;  // the suffix sum, from the outputs' direct dependence on the final transmittance
+  // the suffix sum; the outputs' direct dependence on the final transmittance,
+  // gT Tf, is added where it is used, so that the sum's small first terms are
+  // not rounded against it
+  float S = 0.f;
 
   // batches back to front; positions are relative to range.x
   const int n_batches = static_cast<int>((n_max + NB - 1) / NB);
@@ -610,7 +616,7 @@ __device__ __forceinline__ void blend_bwd_item(const BackArgs& a, const int item
             // gradient arithmetic (not a blend decision): fused multiply-adds
             float h = fmaf(gC[0], col.x, fmaf(gC[1], col.y, fmaf(gC[2], col.z, hq[half * kBwdHalf + q])));
             if constexpr (!PO) h = fmaf(GZ, opz.z, h);
-            const float dA = fmaf(T, h, -(S * iom));
+            const float dA = fmaf(T, h, -(fmaf(gT, Tf, S) * iom));
             S = fmaf(w, h, S);
             dpow = oG <= kAlphaMax ? dA * alpha : 0.f;
           }
@@ -623,10 +629,11 @@ __device__ __forceinline__ void blend_bwd_item(const BackArgs& a, const int item
           const int s = lane & 7, row = lane >> 3;
           const int e = h0 + s;
           const int slot = s_list[wave][min(e, n_mine - 1)];
-          const float2 uv = *reinterpret_cast<const float2*>(&s_sp[slot][0]);
-          const float x0 = static_cast<float>(bx0) + 0.5f - uv.x;
-          const float dy = static_cast<float>(by0 + row) + 0.5f - uv.y;
-          float m0 = 0.f, m1 = 0.f, m2 = 0.f, c[4] = {0.f, 0.f, 0.f, 0.f};
+          const float4 geo = s_sp[slot][0];
+          const float x0 = static_cast<float>(bx0) + 0.5f - geo.x;
+          const float dy = static_cast<float>(by0 + row) + 0.5f - geo.y;
+          const float bdy = geo.w * dy, cdy = s_sp[slot][1].x * dy;
+          float m0 = 0.f, m1 = 0.f, m2 = 0.f, su = 0.f, sv = 0.f, c[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
           for (int i4 = 0; i4 < 2; ++i4) {
             const float4 d4 = *reinterpret_cast<const float4*>(&s_d[wave][s][8 * row + 4 * i4]);
@@ -639,6 +646,8 @@ __device__ __forceinline__ void blend_bwd_item(const BackArgs& a, const int item
               m0 += dv[i];
               m1 += t;
               m2 = fmaf(t, dx, m2);
+              su = fmaf(dv[i], fmaf(geo.z, dx, bdy), su);
+              sv = fmaf(dv[i], fmaf(geo.w, dx, cdy), sv);
             }
 #pragma unroll
             for (int k = 0; k < (PO ? 3 : 4); ++k) {
@@ -653,7 +662,7 @@ __device__ __forceinline__ void blend_bwd_item(const BackArgs& a, const int item
               }
             }
           }
-          const float v[8] = {m1, m0 * dy, m2, m1 * dy, m0 * dy * dy, c[0], c[1], c[2]};
+          const float v[8] = {su, sv, m2, m1 * dy, m0 * dy * dy, c[0], c[1], c[2]};
           const float tot = octet_scatter8(v, lane);
           const int k = lane >> 3;
           if (e < n_mine) s_g[wave][k * GR + slot] = tot;
@@ -721,7 +730,7 @@ __device__ __forceinline__ void blend_bwd_item(const BackArgs& a, const int item
 #pragma unroll
       for (int w = 0; w < NW; ++w)
         if ((s_hits[w] >> slot) & 1u) v += s_g[w][k * GR + slot];
-      // rows: d dx, d dy, d dx^2, d dx dy, d dy^2, w gC (3), d, w gZ
+      // rows: d (a dx + b dy), d (b dx + c dy), d dx^2, d dx dy, d dy^2, w gC (3), d, w gZ
       const int at = k < 5 ? k : (k < 8 ? k + 2 : k - 3);
       if (v != 0.f)
         atomicAdd(a.g_rec + static_cast<int64_t>(__float_as_uint(s_sp[slot][3].x)) * kGradRecStride + at, v);
@@ -912,10 +921,10 @@ __device__ __forceinline__ void record_grad(const ProjBackArgs& a, const int pos
     const int64_t idx = static_cast<int64_t>(pose) * a.rec_cap + slot;
     const float* gr = a.g_rec + idx * kGradRecStride;
     const Splat sp = a.recs[idx];
-    // from the moments of dL/dpower over the splat's pixels: power is
+    // from the sums of dL/dpower over the splat's pixels: power is
     // -(ca dx^2 + cc dy^2) / 2 - cb dx dy with dx, dy from the mean, and
     // alpha = o e^power
-    const float g_u = fmaf(sp.ca, gr[0], sp.cb * gr[1]), g_v = fmaf(sp.cb, gr[0], sp.cc * gr[1]);
+    const float g_u = gr[0], g_v = gr[1];
     const float g_ca = -0.5f * gr[2], g_cb = -gr[3], g_cc = -0.5f * gr[4], g_o = gr[5] / sp.o, g_z = gr[6];
     const float gcol[3] = {gr[7], gr[8], gr[9]};
     const int64_t i = sp.gid;

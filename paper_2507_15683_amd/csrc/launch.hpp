@@ -122,7 +122,8 @@ struct BackArgs {
   const float* g_alpha;
   const float* g_feat;
   // per record, d = dL/dpower and w = alpha T at a pixel, sums over pixels of
-  // d dx, d dy, d dx^2, d dx dy, d dy^2, d, w gZ, w gC (3) (+2 pad)
+  // d (a dx + b dy), d (b dx + c dy), d dx^2, d dx dy, d dy^2, d, w gZ, w gC (3)
+  // (+2 pad), with the conic a, b, c
   float* g_rec;
   float* g_featvec;          // n x D or null
   const int32_t* flags;
