@@ -167,17 +167,20 @@ __device__ __forceinline__ void blend_bwd_item(const BackArgs& a, const int item
   constexpr int FBS = D > 0 ? D / 2 + 4 : 4;   // words per staged bf16 feature vector (padded)
   constexpr int WR = FEATGRAD ? kBwdGroup : kBwdHalf;  // rows of weights kept
   constexpr int GS = D + 1;                    // FEATGRAD: words per pixel's gradient and per splat's feature sum
+  struct alignas(16) Wave {                    // what a wave keeps to itself, at constant offsets from one address
+    float d[kBwdHalf][ROW];                    // dL/dpower per splat (row) and pixel
+    float w[WR][ROW];                          // blend weight
+    float gc[PO ? 3 : 4][8 * kBwdGcRow];       // gC, gZ planes of the wave's 8x8 pixels
+    float g[NV * GR];                          // per staged splat: its sums (where the wave hit it)
+    uint8_t list[NB];                          // slots of the wave's hits, back to front
+  };
   struct Walk {
     float4 sp[NB][4];                          // u v ca cb | cc o z gid | r g b pmin | record index
     uint32_t fb[NB * FBS];                     // bf16 feature vectors
-    float d[NW][kBwdHalf][ROW];                // dL/dpower per splat (row) and pixel
-    float w[NW][WR][ROW];                      // blend weight
-    float gc[NW][PO ? 3 : 4][8 * kBwdGcRow];   // gC, gZ planes of each wave's 8x8 pixels
-    float g[NW][NV * GR];                      // per wave and staged splat: moment sums (where the wave hit it)
+    Wave wave[NW];
     uint64_t hits[NW];                         // the waves' hits of the round
-    float gfe[FEATGRAD ? NB * GS : 1];         // FEATGRAD: and its feature sums
+    float gfe[FEATGRAD ? NB * GS : 1];         // FEATGRAD: feature sums per staged splat
     uint8_t mask[NB];
-    uint8_t list[NW][NB];                      // slots of each wave's hits, back to front
   };
   union Lds {
     Walk walk;
@@ -188,16 +191,12 @@ __device__ __forceinline__ void blend_bwd_item(const BackArgs& a, const int item
   __shared__ float s_lw[NW];
   auto& s_sp = s_u.walk.sp;
   auto& s_fb = s_u.walk.fb;
-  auto& s_d = s_u.walk.d;
-  auto& s_w = s_u.walk.w;
-  auto& s_gc = s_u.walk.gc;
-  auto& s_g = s_u.walk.g;
   auto& s_hits = s_u.walk.hits;
   auto& s_gfe = s_u.walk.gfe;
   auto& s_mask = s_u.walk.mask;
-  auto& s_list = s_u.walk.list;
   const int tid = threadIdx.x;
-  const int lane = tid & (kWave - 1), wave = tid >> 6;
+  const int lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  Wave& own = s_u.walk.wave[wave];
   const int W = a.c.W, H = a.c.H;
   const int64_t HW = static_cast<int64_t>(W) * H;
   const int part = item % Sh::kParts, titem = item / Sh::kParts;
@@ -227,41 +226,60 @@ __device__ __forceinline__ void blend_bwd_item(const BackArgs& a, const int item
   // a round's staging: list entry, then record and feature vector, dealt to
   // the splat's SHARE threads and held in registers until the LDS is free
   constexpr int RV = (3 + SHARE - 1) / SHARE, FV = DV > 0 ? (DV + SHARE - 1) / SHARE : 1;
+  constexpr bool AHEAD = FV <= 4;  // 64 channels at tile 8: a thread's 32 words of features would cost a wave
   const int st_e = tid / SHARE, st_sub = tid % SHARE;
-  uint32_t st_lv = 0, st_gid = 0;
-  float4 st_rec[RV];
-  uint4 st_feat[FV];
-  auto stage_index = [&](uint2 range, uint32_t b0) {
+  uint32_t st_lv = 0;
+  // the thread's quads and features as vector values (arrays of float4 would be kept in scratch memory)
+  floatx4 st_rec0 = {}, st_rec1 = {}, st_rec2 = {};
+  typedef uint32_t featv __attribute__((ext_vector_type(AHEAD ? 4 * FV : 1)));
+  featv st_feat = {};
+  auto stage_index = [&](uint2 range, uint32_t b0) -> uint32_t {  // the Gaussian's index
     const uint32_t j = range.x + b0 + st_e;
+    uint32_t gid = 0;
     if (j < range.y) {
       st_lv = a.list[j];
-      st_gid = a.list_gid[j];
+      if constexpr (DV > 0 && AHEAD) gid = a.list_gid[j];
     }
+    return gid;
   };
-  auto stage_load = [&](uint2 range, uint32_t b0) {
+  auto stage_load = [&](uint2 range, uint32_t b0, uint32_t gid) {
     if (range.x + b0 + st_e < range.y) {
-      const float4* sp = reinterpret_cast<const float4*>(a.recs + (st_lv & kRecMask));
-#pragma unroll
-      for (int q = 0; q < RV; ++q)
-        if (q * SHARE + st_sub < 3) st_rec[q] = sp[q * SHARE + st_sub];
-      if constexpr (DV > 0) {
-        const uint4* fv = reinterpret_cast<const uint4*>(a.feat) + static_cast<int64_t>(st_gid) * DV;
+      int sub = st_sub;
+      asm volatile("" : "+v"(sub));  // keeps the two 64-bit addresses inside the round instead of in registers for the walk
+      const floatx4* sp = reinterpret_cast<const floatx4*>(a.recs + (st_lv & kRecMask));
+      if (sub < 3) st_rec0 = sp[sub];
+      if (RV > 1 && sub + SHARE < 3) st_rec1 = sp[sub + SHARE];
+      if (RV > 2) st_rec2 = sp[2];
+      if constexpr (DV > 0 && AHEAD) {
+        const uint4* fv = reinterpret_cast<const uint4*>(a.feat) + static_cast<int64_t>(gid) * DV;
 #pragma unroll
         for (int q = 0; q < FV; ++q)
-          if (q * SHARE + st_sub < DV) st_feat[q] = fv[q * SHARE + st_sub];
+          if (q * SHARE + sub < DV) {
+            const uint4 f = fv[q * SHARE + sub];
+            st_feat[4 * q] = f.x;
+            st_feat[4 * q + 1] = f.y;
+            st_feat[4 * q + 2] = f.z;
+            st_feat[4 * q + 3] = f.w;
+          }
       }
     }
   };
   auto stage_store = [&](int nb) {
     if (st_e < nb) {
+      floatx4* sp = reinterpret_cast<floatx4*>(s_sp[st_e]);
+      if (st_sub < 3) sp[st_sub] = st_rec0;
+      if (RV > 1 && st_sub + SHARE < 3) sp[st_sub + SHARE] = st_rec1;
+      if (RV > 2) sp[2] = st_rec2;
+      if constexpr (!AHEAD) {  // a thread stages a whole splat: its record holds the Gaussian's index
+        const uint4* fv = reinterpret_cast<const uint4*>(a.feat) + static_cast<int64_t>(__float_as_uint(st_rec1[3])) * DV;
 #pragma unroll
-      for (int q = 0; q < RV; ++q)
-        if (q * SHARE + st_sub < 3) s_sp[st_e][q * SHARE + st_sub] = st_rec[q];
-      if constexpr (DV > 0) {
+        for (int q = 0; q < DV; ++q) reinterpret_cast<uint4*>(&s_fb[st_e * FBS])[q] = fv[q];
+      } else if constexpr (DV > 0) {
 #pragma unroll
         for (int q = 0; q < FV; ++q)
           if (q * SHARE + st_sub < DV)
-            reinterpret_cast<uint4*>(&s_fb[st_e * FBS])[q * SHARE + st_sub] = st_feat[q];
+            reinterpret_cast<uint4*>(&s_fb[st_e * FBS])[q * SHARE + st_sub] =
+                make_uint4(st_feat[4 * q], st_feat[4 * q + 1], st_feat[4 * q + 2], st_feat[4 * q + 3]);
       }
       if (st_sub == SHARE - 1) {
         s_sp[st_e][3].x = __uint_as_float(st_lv & kRecMask);
@@ -360,7 +378,7 @@ __device__ __forceinline__ void blend_bwd_item(const BackArgs& a, const int item
   // the list's last round is the first one walked, unless every pixel stopped
   // before it
   uint32_t staged = range.y > range.x ? (range.y - range.x - 1) / NB * NB : 0u;
-  if (range.y > range.x) stage_index(range, staged);
+  const uint32_t gid0 = range.y > range.x ? stage_index(range, staged) : 0u;
   __builtin_amdgcn_sched_barrier(0);
 
   T = Tf;
@@ -421,7 +439,7 @@ __device__ __forceinline__ void blend_bwd_item(const BackArgs& a, const int item
 #pragma unroll
       for (int s = 0; s < CG; ++s) gb[s][b] = fmaf(f1[b], gt[s][b], f2[b] * gb[s][b]);
   }
-  if (range.y > range.x) stage_load(range, staged);  // its records travel while the prologue ends
+  if (range.y > range.x) stage_load(range, staged, gid0);  // its records travel while the prologue ends
   // the gradients in three bf16 parts that sum to them exactly (top, middle and
   // last 8 significant bits)
   uint32_t gq[KS][3][4][KW] = {};
@@ -481,8 +499,8 @@ __device__ __forceinline__ void blend_bwd_item(const BackArgs& a, const int item
   {
     const int at = (lane >> 3) * kBwdGcRow + (lane & 7);
 #pragma unroll
-    for (int c = 0; c < 3; ++c) s_gc[wave][c][at] = gC[c];
-    if constexpr (!PO) s_gc[wave][PO ? 0 : 3][at] = GZ;
+    for (int c = 0; c < 3; ++c) own.gc[c][at] = gC[c];
+    if constexpr (!PO) own.gc[PO ? 0 : 3][at] = GZ;
   }
   if constexpr (FEATGRAD) {
     for (int e = tid; e < NB * GS; e += NT) s_gfe[e] = 0.f;
@@ -509,10 +527,7 @@ __device__ __forceinline__ void blend_bwd_item(const BackArgs& a, const int item
   for (int bi = n_batches - 1; bi >= 0; --bi) {
     const uint32_t b0 = static_cast<uint32_t>(bi) * NB;
     const int nb = static_cast<int>(min(static_cast<uint32_t>(NB), n_max - b0));
-    if (staged != b0) {
-      stage_index(range, b0);
-      stage_load(range, b0);
-    }
+    if (staged != b0) stage_load(range, b0, stage_index(range, b0));
     stage_store(nb);
     __syncthreads();
     // the batch's splats that meet this wave's block and lie below its largest
@@ -524,15 +539,14 @@ __device__ __forceinline__ void blend_bwd_item(const BackArgs& a, const int item
       const bool hit = lane < nb && b0 + lane < wave_max && ((s_mask[lane] >> mask_bit) & 1u);
       todo = __ballot(hit);
       n_mine = __popcll(todo);
-      if (hit) s_list[wave][__popcll(todo >> lane) - 1] = static_cast<uint8_t>(lane);
+      if (hit) own.list[__popcll(todo >> lane) - 1] = static_cast<uint8_t>(lane);
       if (lane == 0) s_hits[wave] = todo;
     }
     wave_lds_fence();
     // the next round's splats travel while this one's are walked
     if (bi > 0) {
       staged = b0 - NB;
-      stage_index(range, staged);
-      stage_load(range, staged);
+      stage_load(range, staged, stage_index(range, staged));
     }
     for (int g0 = 0; g0 < n_mine; g0 += kBwdGroup) {
       // h's feature part of 16 splats: hq[q] for this lane's pixel
@@ -540,7 +554,7 @@ __device__ __forceinline__ void blend_bwd_item(const BackArgs& a, const int item
 #pragma unroll
       for (int q = 0; q < kBwdGroup; ++q) hq[q] = 0.f;
       if constexpr (D > 0) {
-        const int js = s_list[wave][min(g0 + (lane & 15), n_mine - 1)];
+        const int js = own.list[min(g0 + (lane & 15), n_mine - 1)];
         floatx4 acc[4] = {};
         const uint32_t* fw = &s_fb[js * FBS + (CG / 2) * (lane >> 4)];
 #pragma unroll
@@ -620,15 +634,15 @@ __device__ __forceinline__ void blend_bwd_item(const BackArgs& a, const int item
             S = fmaf(w, h, S);
             dpow = oG <= kAlphaMax ? dA * alpha : 0.f;
           }
-          s_d[wave][q][lane] = dpow;
-          s_w[wave][wrow + q][lane] = w;
+          own.d[q][lane] = dpow;
+          own.w[wrow + q][lane] = w;
         }
         wave_lds_fence();
         // transposed: lane l takes splat l % 8's pixel row l / 8 of the block
         {
           const int s = lane & 7, row = lane >> 3;
           const int e = h0 + s;
-          const int slot = s_list[wave][min(e, n_mine - 1)];
+          const int slot = own.list[min(e, n_mine - 1)];
           const float4 geo = s_sp[slot][0];
           const float x0 = static_cast<float>(bx0) + 0.5f - geo.x;
           const float dy = static_cast<float>(by0 + row) + 0.5f - geo.y;
@@ -636,8 +650,8 @@ __device__ __forceinline__ void blend_bwd_item(const BackArgs& a, const int item
           float m0 = 0.f, m1 = 0.f, m2 = 0.f, su = 0.f, sv = 0.f, c[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
           for (int i4 = 0; i4 < 2; ++i4) {
-            const float4 d4 = *reinterpret_cast<const float4*>(&s_d[wave][s][8 * row + 4 * i4]);
-            const float4 w4 = *reinterpret_cast<const float4*>(&s_w[wave][wrow + s][8 * row + 4 * i4]);
+            const float4 d4 = *reinterpret_cast<const float4*>(&own.d[s][8 * row + 4 * i4]);
+            const float4 w4 = *reinterpret_cast<const float4*>(&own.w[wrow + s][8 * row + 4 * i4]);
             const float dv[4] = {d4.x, d4.y, d4.z, d4.w}, wv[4] = {w4.x, w4.y, w4.z, w4.w};
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
@@ -651,7 +665,7 @@ __device__ __forceinline__ void blend_bwd_item(const BackArgs& a, const int item
             }
 #pragma unroll
             for (int k = 0; k < (PO ? 3 : 4); ++k) {
-              const float4 g4 = *reinterpret_cast<const float4*>(&s_gc[wave][k][row * kBwdGcRow + 4 * i4]);
+              const float4 g4 = *reinterpret_cast<const float4*>(&own.gc[k][row * kBwdGcRow + 4 * i4]);
               const float gv[4] = {g4.x, g4.y, g4.z, g4.w};
               if (!bad) {
 #pragma unroll
@@ -665,10 +679,10 @@ __device__ __forceinline__ void blend_bwd_item(const BackArgs& a, const int item
           const float v[8] = {su, sv, m2, m1 * dy, m0 * dy * dy, c[0], c[1], c[2]};
           const float tot = octet_scatter8(v, lane);
           const int k = lane >> 3;
-          if (e < n_mine) s_g[wave][k * GR + slot] = tot;
+          if (e < n_mine) own.g[k * GR + slot] = tot;
           if constexpr (!PO) {
             const float t2 = octet_sum2(m0, c[3]);
-            if ((lane & 31) < 8 && e < n_mine) s_g[wave][(lane < 32 ? NV - 2 : NV - 1) * GR + slot] = t2;
+            if ((lane & 31) < 8 && e < n_mine) own.g[(lane < 32 ? NV - 2 : NV - 1) * GR + slot] = t2;
           }
         }
         wave_lds_fence();  // the rows are rewritten by the next half
@@ -679,7 +693,7 @@ __device__ __forceinline__ void blend_bwd_item(const BackArgs& a, const int item
         floatx4 acc[NBL] = {};
 #pragma unroll
         for (int i4 = 0; i4 < 4; ++i4) {
-          const float4 w4 = *reinterpret_cast<const float4*>(&s_w[wave][ch][16 * q4 + 4 * i4]);
+          const float4 w4 = *reinterpret_cast<const float4*>(&own.w[ch][16 * q4 + 4 * i4]);
           const float wv[4] = {w4.x, w4.y, w4.z, w4.w};
 #pragma unroll
           for (int i = 0; i < 4; ++i)
@@ -702,7 +716,7 @@ __device__ __forceinline__ void blend_bwd_item(const BackArgs& a, const int item
                 const float g = __shfl(gB[bl][i], 16 * k + ch, kWave);
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                  const float wv = s_w[wave][4 * q4 + r][p];
+                  const float wv = own.w[4 * q4 + r][p];
                   if (wv != 0.f) acc[bl][r] = fmaf(wv, g, acc[bl][r]);
                 }
               }
@@ -712,7 +726,7 @@ __device__ __forceinline__ void blend_bwd_item(const BackArgs& a, const int item
         for (int r = 0; r < 4; ++r) {
           const int e = g0 + 4 * q4 + r;
           if (e < n_mine) {
-            const int slot = s_list[wave][e];
+            const int slot = own.list[e];
 #pragma unroll
             for (int bl = 0; bl < NBL; ++bl)
               if (16 * bl + ch < D) atomicAdd(&s_gfe[slot * GS + 16 * bl + ch], acc[bl][r]);
@@ -724,19 +738,21 @@ __device__ __forceinline__ void blend_bwd_item(const BackArgs& a, const int item
     __syncthreads();
     // one global atomic per nonzero sum of the round: the waves that hit the
     // splat, in order
-    for (int e = tid; e < nb * NV; e += NT) {
+    int first = tid;
+    asm volatile("" : "+v"(first));  // keeps what follows from it inside the round
+    for (int e = first; e < nb * NV; e += NT) {
       const int slot = e / NV, k = e - slot * NV;
       float v = 0.f;
 #pragma unroll
       for (int w = 0; w < NW; ++w)
-        if ((s_hits[w] >> slot) & 1u) v += s_g[w][k * GR + slot];
+        if ((s_hits[w] >> slot) & 1u) v += s_u.walk.wave[w].g[k * GR + slot];
       // rows: d (a dx + b dy), d (b dx + c dy), d dx^2, d dx dy, d dy^2, w gC (3), d, w gZ
       const int at = k < 5 ? k : (k < 8 ? k + 2 : k - 3);
       if (v != 0.f)
         atomicAdd(a.g_rec + static_cast<int64_t>(__float_as_uint(s_sp[slot][3].x)) * kGradRecStride + at, v);
     }
     if constexpr (FEATGRAD) {
-      for (int e = tid; e < nb * D; e += NT) {
+      for (int e = first; e < nb * D; e += NT) {
         const int slot = e / D, d = e - slot * D;
         const float v = s_gfe[slot * GS + d];
         if (v != 0.f) {
