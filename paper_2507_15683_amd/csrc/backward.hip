@@ -15,6 +15,8 @@
 // pinhole Jacobian, the camera transform and the SH view direction, into
 // dL/d(mean, opacity, scales, rotation, SH) and the pose's left-perturbation
 // tangent (rho, phi), block-reduced per pose.
+#include <type_traits>
+
 #include "hgsr_device.hpp"
 #include "launch.hpp"
 
@@ -188,6 +190,7 @@ __device__ __forceinline__ void blend_bwd_item(const BackArgs& a, const int item
   };
   __shared__ __align__(16) Lds s_u;
   __shared__ uint32_t s_max;
+  __shared__ uint32_t s_odd;  // ODD: a staged feature of the round is not finite
   __shared__ float s_lw[NW];
   auto& s_sp = s_u.walk.sp;
   auto& s_fb = s_u.walk.fb;
@@ -226,6 +229,12 @@ __device__ __forceinline__ void blend_bwd_item(const BackArgs& a, const int item
   // a round's staging: list entry, then record and feature vector, dealt to
   // the splat's SHARE threads and held in registers until the LDS is free
   constexpr int RV = (3 + SHARE - 1) / SHARE, FV = DV > 0 ? (DV + SHARE - 1) / SHARE : 1;
+  // Infinities in the feature term, where the caller gives the gradients (the
+  // residual's own are NaN wherever a map is not finite): an FP32 product gives
+  // an infinity, the parts' products 0 times infinity as well.  A part of an
+  // infinite gradient beyond the first is zero, and beside such a feature the
+  // second and third parts meet a zero instead.
+  constexpr bool ODD = !RES && D > 0;
   constexpr bool AHEAD = FV <= 4;  // 64 channels at tile 8: a thread's 32 words of features would cost a wave
   const int st_e = tid / SHARE, st_sub = tid % SHARE;
   uint32_t st_lv = 0;
@@ -273,13 +282,19 @@ __device__ __forceinline__ void blend_bwd_item(const BackArgs& a, const int item
       if constexpr (!AHEAD) {  // a thread stages a whole splat: its record holds the Gaussian's index
         const uint4* fv = reinterpret_cast<const uint4*>(a.feat) + static_cast<int64_t>(__float_as_uint(st_rec1[3])) * DV;
 #pragma unroll
-        for (int q = 0; q < DV; ++q) reinterpret_cast<uint4*>(&s_fb[st_e * FBS])[q] = fv[q];
+        for (int q = 0; q < DV; ++q) {
+          const uint4 f = fv[q];
+          if (ODD && nonfinite_bf16x8(f)) s_odd = 1;
+          reinterpret_cast<uint4*>(&s_fb[st_e * FBS])[q] = f;
+        }
       } else if constexpr (DV > 0) {
 #pragma unroll
         for (int q = 0; q < FV; ++q)
-          if (q * SHARE + st_sub < DV)
-            reinterpret_cast<uint4*>(&s_fb[st_e * FBS])[q * SHARE + st_sub] =
-                make_uint4(st_feat[4 * q], st_feat[4 * q + 1], st_feat[4 * q + 2], st_feat[4 * q + 3]);
+          if (q * SHARE + st_sub < DV) {
+            const uint4 f = make_uint4(st_feat[4 * q], st_feat[4 * q + 1], st_feat[4 * q + 2], st_feat[4 * q + 3]);
+            if (ODD && nonfinite_bf16x8(f)) s_odd = 1;
+            reinterpret_cast<uint4*>(&s_fb[st_e * FBS])[q * SHARE + st_sub] = f;
+          }
       }
       if (st_sub == SHARE - 1) {
         s_sp[st_e][3].x = __uint_as_float(st_lv & kRecMask);
@@ -288,6 +303,7 @@ __device__ __forceinline__ void blend_bwd_item(const BackArgs& a, const int item
     }
   };
   if (tid == 0) s_max = 0;
+  if (ODD && tid == 0) s_odd = 0;
   const int px = bx0 + (lane & 7), py = by0 + (lane >> 3);
   const float pxf = static_cast<float>(px) + 0.5f, pyf = static_cast<float>(py) + 0.5f;
   const int64_t po = static_cast<int64_t>(pose) * HW;
@@ -443,7 +459,7 @@ __device__ __forceinline__ void blend_bwd_item(const BackArgs& a, const int item
   // the gradients in three bf16 parts that sum to them exactly (top, middle and
   // last 8 significant bits)
   uint32_t gq[KS][3][4][KW] = {};
-  auto split_operands = [&]() {
+  auto split_operands = [&](auto inf) {
 #pragma unroll
     for (int b = 0; b < 4; ++b)
 #pragma unroll
@@ -453,12 +469,26 @@ __device__ __forceinline__ void blend_bwd_item(const BackArgs& a, const int item
         for (int q = 0; q < 3; ++q) {
           gq[s / 8][q][b][(s % 8) / 2] =
               __builtin_amdgcn_perm(__float_as_uint(y), __float_as_uint(x), 0x07060302u);  // the top halves
-          x -= __uint_as_float(__float_as_uint(x) & 0xffff0000u);
-          y -= __uint_as_float(__float_as_uint(y) & 0xffff0000u);
+          const float hx = __uint_as_float(__float_as_uint(x) & 0xffff0000u);
+          const float hy = __uint_as_float(__float_as_uint(y) & 0xffff0000u);
+          x = inf.value && x == hx ? 0.f : x - hx;
+          y = inf.value && y == hy ? 0.f : y - hy;
         }
       }
   };
-  if constexpr (D > 0) split_operands();
+  bool odd_gf = false;  // uniform: a feature gradient of the wave's block is not finite
+  if constexpr (ODD) {
+    float zero = 0.f;
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+      for (int s = 0; s < CG; ++s) zero = fmaf(gb[s][b], 0.f, zero);
+    odd_gf = __any(zero != zero);
+    if (odd_gf) split_operands(std::true_type{});
+    else split_operands(std::false_type{});
+  } else if constexpr (D > 0) {
+    split_operands(std::false_type{});
+  }
   // list positions this wave must visit: below the largest saved length
   uint32_t wave_max = last;
 #pragma unroll
@@ -483,8 +513,10 @@ __device__ __forceinline__ void blend_bwd_item(const BackArgs& a, const int item
           const int c = 16 * bl + (lane & 15);
           if (c < D) gB[bl][i] = gf[(16 * (lane >> 4) + i) * GS + c];
         }
+      if (RES || odd_gf) {
 #pragma unroll 4
-      for (int c = 0; c < D; ++c) nonfinite |= !finite_bits(gf[lane * GS + c]);
+        for (int c = 0; c < D; ++c) nonfinite |= !finite_bits(gf[lane * GS + c]);
+      }
     }
   }
   __syncthreads();  // s_max cleared; the walk's staging takes the LDS
@@ -530,6 +562,7 @@ __device__ __forceinline__ void blend_bwd_item(const BackArgs& a, const int item
     if (staged != b0) stage_load(range, b0, stage_index(range, b0));
     stage_store(nb);
     __syncthreads();
+    const bool odd = ODD && __builtin_amdgcn_readfirstlane(s_odd) != 0;
     // the batch's splats that meet this wave's block and lie below its largest
     // saved length, as a mask (the walk) and a list, back to front (the
     // per-lane lookups)
@@ -567,22 +600,34 @@ __device__ __forceinline__ void blend_bwd_item(const BackArgs& a, const int item
             av[0] = fw[0];
             if constexpr (CG > 2) av[1] = fw[1];
           }
+          auto product = [&](const uint32_t (&a0)[KW], const uint32_t (&a12)[KW]) {
 #pragma unroll
-          for (int q = 2; q >= 0; --q)
+            for (int q = 2; q >= 0; --q)
 #pragma unroll
-            for (int b = 0; b < 4; ++b) {
-              if constexpr (KW == 4) {
-                bf16x8 A, B;
-                __builtin_memcpy(&A, av, 16);
-                __builtin_memcpy(&B, gq[ks][q][b], 16);
-                acc[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A, B, acc[b], 0, 0, 0);
-              } else {
-                shortx4 A, B;
-                __builtin_memcpy(&A, av, 8);
-                __builtin_memcpy(&B, gq[ks][q][b], 8);
-                acc[b] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(A, B, acc[b], 0, 0, 0);
+              for (int b = 0; b < 4; ++b) {
+                if constexpr (KW == 4) {
+                  bf16x8 A, B;
+                  __builtin_memcpy(&A, q ? a12 : a0, 16);
+                  __builtin_memcpy(&B, gq[ks][q][b], 16);
+                  acc[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A, B, acc[b], 0, 0, 0);
+                } else {
+                  shortx4 A, B;
+                  __builtin_memcpy(&A, q ? a12 : a0, 8);
+                  __builtin_memcpy(&B, gq[ks][q][b], 8);
+                  acc[b] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(A, B, acc[b], 0, 0, 0);
+                }
               }
-            }
+          };
+          if (odd) {  // uniform
+            uint32_t finite[KW];
+#pragma unroll
+            for (int t = 0; t < KW; ++t)
+              finite[t] = av[t] & (((av[t] & 0x7f80u) == 0x7f80u ? 0u : 0xffffu) |
+                                   ((av[t] & 0x7f800000u) == 0x7f800000u ? 0u : 0xffff0000u));
+            product(av, finite);
+          } else {
+            product(av, av);
+          }
         }
         // lane l, register r of block b: splat 4 (l / 16) + r, pixel
         // 16 b + l % 16 -> this lane's pixel
@@ -736,6 +781,7 @@ __device__ __forceinline__ void blend_bwd_item(const BackArgs& a, const int item
       }
     }
     __syncthreads();
+    if (ODD && tid == 0) s_odd = 0;  // read by every wave; the next round's staging waits below
     // one global atomic per nonzero sum of the round: the waves that hit the
     // splat, in order
     int first = tid;

@@ -339,14 +339,11 @@ __device__ __forceinline__ void wave_lds_fence() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Whether either of two packed bfloat16 values is infinite or NaN.
-__device__ __forceinline__ bool nonfinite_bf16x2(uint32_t w) {
-  return (w & 0x7f80u) == 0x7f80u || (w & 0x7f800000u) == 0x7f800000u;
-}
-
-// Whether any of eight packed bfloat16 values is.
+// Whether any of eight packed bfloat16 values is infinite or NaN: an exponent
+// of all ones, and no other, carries into the sign's place.
 __device__ __forceinline__ bool nonfinite_bf16x8(const uint4& f) {
-  return nonfinite_bf16x2(f.x) || nonfinite_bf16x2(f.y) || nonfinite_bf16x2(f.z) || nonfinite_bf16x2(f.w);
+  auto carry = [](uint32_t w) { return (w & 0x7f807f80u) + 0x00800080u; };
+  return ((carry(f.x) | carry(f.y) | carry(f.z) | carry(f.w)) & 0x80008000u) != 0;
 }
 
 // Smallest conic distance q(p - mean) = a dx^2 + 2 b dx dy + c dy^2 over the

@@ -1,7 +1,7 @@
 """GPU backward against a dense 64-bit evaluation with autograd on the CPU
 (every pixel against every Gaussian, no tiles and no lists), over lists of
-several staging rounds; the summation error of the mean gradient; one shared
-target over several pose blocks."""
+several staging rounds; the summation error of the mean gradient; infinite
+features and output gradients; one shared target over several pose blocks."""
 import math
 
 import numpy as np
@@ -191,6 +191,38 @@ def test_mean_gradient_of_needles(hg, length, turn, tile):
         scale = np.abs(dpow * term).sum() * f / z
         log("error of the sum, in 2^-24 of the terms:", abs(g[k]) / scale * 2 ** 24)
         assert abs(g[k]) <= 18 * 2.0 ** -24 * scale, k
+
+
+@pytest.mark.parametrize("tile", [8, 16, 32])
+@pytest.mark.parametrize("D", [8, 16, 32, 64])
+def test_infinite_feature_or_gradient_gives_infinities(hg, D, tile):
+    """Three concentric splats, dL/dfeat = 1.  h is the pixel gradient times
+    the feature, so an infinite feature of the middle splat makes its opacity
+    gradient +infinity, that of the splat before it -infinity (its suffix sum)
+    and leaves the one behind finite; an infinite pixel gradient and positive
+    features make that of the last splat +infinity."""
+    import torch
+    n = 3
+    feat = np.full((n, D), 0x3F80, np.uint16)  # 1.0
+    sc = synth.Scene(means=np.array([[0, 0, 9], [0, 0, 10], [0, 0, 11]], np.float32),
+                     log_scales=np.full((n, 3), -1.0, np.float32), quats=np.tile(np.float32([1, 0, 0, 0]), (n, 1)),
+                     opacities=np.full(n, 0.5, np.float32), sh=np.ones((n, 1, 3), np.float32), sh_degree=0, feat=feat)
+    K = hg.Intrinsics(100.0, 100.0, 20.0, 18.0, 40, 36)
+    pose = _t(np.array([[1, 0, 0, 0, 0, 1, 0, 0, 0, 0, 1, 0]], np.float32))
+    r = hg.Renderer()
+    for piece in range(D // 8):
+        log(f"case: infinite feature D={D} tile={tile} piece {piece}")
+        sc.feat[:] = 0x3F80
+        sc.feat[1, 8 * piece + 5] = 0x7F80
+        out = r.render(hg.GaussianScene.from_numpy(sc), pose, K, tile=tile)
+        g = to_np(r.backward(dict(feat=torch.ones_like(out["feat"])), want=("opacities",))["opacities"])
+        assert g[0] == -math.inf and g[1] == math.inf and math.isfinite(g[2]), g
+        sc.feat[:] = 0x3F80
+        out = r.render(hg.GaussianScene.from_numpy(sc), pose, K, tile=tile)
+        go = torch.ones_like(out["feat"])
+        go[0, 8 * piece + 2] = math.inf
+        g = to_np(r.backward(dict(feat=go), want=("opacities",))["opacities"])
+        assert g[2] == math.inf, g
 
 
 def test_shared_target_over_several_pose_blocks(hg):
