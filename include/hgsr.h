@@ -667,7 +667,9 @@ hgsr_status hgsr_debug_tile_lists(hgsr_ctx* ctx, int32_t pose, uint32_t* ranges,
  * the context's default (opts->tile == 0, opts->schedule == HGSR_SCHED_AUTO,
  * opts->feat_accum == HGSR_FEAT_AUTO) and append it to the JSON-lines cache
  * file `cache_path` (host string, may be NULL), which later calls on the same
- * shape read instead of timing.  with_backward != 0 times each render
+ * shape and output type by the same build of the library read instead of
+ * timing.  The feature accumulation is kept per width (32 and 64 channels; the
+ * others have one form).  with_backward != 0 times each render
  * followed by the pose backward (dL/drgb and, for FP32 feature maps,
  * dL/dfeat taken as the rendered maps themselves), the cost of a refinement
  * step, instead of the render alone.  Synchronises `stream`. */

@@ -1,6 +1,7 @@
 """Build the HIP library libhgsr.so for gfx950 in-tree with hipcc."""
 from __future__ import annotations
 
+import hashlib
 import os
 import subprocess
 import sys
@@ -31,16 +32,27 @@ FILE_FLAGS = {"match.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
               "blend.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 
 
+def sources_id() -> str:
+    """Names the kernels (sources and flags): choices timed with others do not hold for them."""
+    h = hashlib.sha256(repr((FLAGS[:-1], FILE_FLAGS)).encode())
+    for name in sorted(os.listdir(CSRC)):
+        with open(os.path.join(CSRC, name), "rb") as f:
+            h.update(name.encode() + b"\0" + f.read())
+    return h.hexdigest()[:12]
+
+
 def build(verbose: bool = False) -> str:
     os.makedirs(BUILD, exist_ok=True)
     srcs = [s for s in SOURCES if os.path.exists(os.path.join(CSRC, s))]
+    file_flags = dict(FILE_FLAGS)
+    file_flags["hgsr_runtime.hip"] = [f'-DHGSR_SOURCES="{sources_id()}"']
 
     def compile_one(src):
         obj = os.path.join(BUILD, os.path.splitext(src)[0] + ".o")
         if src.endswith(".cpp"):  # host-only C++
             cmd = ["g++", *HOST_FLAGS, "-c", os.path.join(CSRC, src), "-o", obj]
         else:
-            cmd = ["hipcc", *FLAGS, *FILE_FLAGS.get(src, []), "-c", os.path.join(CSRC, src), "-o", obj]
+            cmd = ["hipcc", *FLAGS, *file_flags.get(src, []), "-c", os.path.join(CSRC, src), "-o", obj]
         if verbose:
             print(" ".join(cmd), flush=True)
         subprocess.check_call(cmd)

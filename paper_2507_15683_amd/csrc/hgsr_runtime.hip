@@ -18,6 +18,10 @@
 
 using namespace hgsr;
 
+#ifndef HGSR_SOURCES  // the build passes a hash of the kernels' sources
+#define HGSR_SOURCES "unnamed"
+#endif
+
 namespace {
 
 thread_local std::string g_err;
@@ -53,6 +57,10 @@ int ilog2(int v) {
   while ((1 << s) < v) ++s;
   return s;
 }
+
+// Whether a feature width is summed in either of two forms (the others have
+// only the FMA form, so tuning on them says nothing about these).
+bool has_feat_forms(int D) { return D == 32 || D == 64; }
 
 int bits_for(uint64_t n) {
   int b = 0;
@@ -99,7 +107,7 @@ struct hgsr_ctx {
   // autotuned defaults
   int tuned_tile = 0;
   int tuned_sched = -1;
-  int tuned_feat = 0;
+  int tuned_feat[2] = {};  // 32 and 64 channels: the widths that have two forms
   int tuned_proj = 0;  // Gaussians per thread of the few-pose projection (0: default 1, the spatial layout's)
 
   // stage timing
@@ -549,7 +557,8 @@ static hgsr_status render_impl(hgsr_ctx* c, const hgsr_gaussians* g, const float
   bl.list_gid = c->sorted_gid;
   {
     int fa = opts->feat_accum;
-    if (fa == HGSR_FEAT_AUTO) fa = c->tuned_feat ? c->tuned_feat : HGSR_FEAT_MFMA;
+    if (fa == HGSR_FEAT_AUTO && has_feat_forms(g->feat_dim)) fa = c->tuned_feat[g->feat_dim == 64];
+    if (fa == HGSR_FEAT_AUTO) fa = HGSR_FEAT_MFMA;
     bl.feat_mfma = fa == HGSR_FEAT_MFMA ? 1 : 0;
   }
   bl.recs = c->recs.as<Splat>();
@@ -1366,9 +1375,14 @@ hgsr_status hgsr_autotune(hgsr_ctx* c, const hgsr_gaussians* g, const float* pos
     const hgsr_grad_outputs go = {out->rgb, nullptr, nullptr, nullptr};
     return hgsr_render_backward(c, &go, &gr, stream);
   };
+  // a choice holds for the kernels it was timed with, so the key names them
   char key[256];
-  snprintf(key, sizeof(key), "\"key\": \"gfx950/%dx%d/P%d/n%lld/D%d/sh%d/sort%d/bwd%d\"", K->width, K->height, P,
-           static_cast<long long>(g->n), g->feat_dim, g->sh_degree, opts->sort_mode, with_backward ? 1 : 0);
+  snprintf(key, sizeof(key), "\"key\": \"gfx950/" HGSR_SOURCES "/%dx%d/P%d/n%lld/D%d/sh%d/sort%d/bf16%d/bwd%d\"",
+           K->width, K->height, P, static_cast<long long>(g->n), g->feat_dim, g->sh_degree, opts->sort_mode,
+           opts->feat_out_bf16 ? 1 : 0, with_backward ? 1 : 0);
+  auto keep_feat = [&](int fa) {
+    if (has_feat_forms(g->feat_dim)) c->tuned_feat[g->feat_dim == 64] = fa;
+  };
   // cached answer?
   if (cache_path) {
     FILE* f = fopen(cache_path, "r");
@@ -1396,7 +1410,7 @@ hgsr_status hgsr_autotune(hgsr_ctx* c, const hgsr_gaussians* g, const float* pos
           (pg == 1 || pg == 4)) {
         c->tuned_tile = t;
         c->tuned_sched = sc;
-        c->tuned_feat = fa;
+        keep_feat(fa);
         c->tuned_proj = pg;
         if (result) *result = {t, sc, fa, ms, pg};
         return HGSR_OK;
@@ -1416,7 +1430,7 @@ hgsr_status hgsr_autotune(hgsr_ctx* c, const hgsr_gaussians* g, const float* pos
     for (int sc : scheds)
       for (int fa : feats) {
       if (P == 1 && sc == HGSR_SCHED_TILE_MAJOR) continue;
-      if (fa == HGSR_FEAT_MFMA && g->feat_dim != 32 && g->feat_dim != 64) continue;
+      if (fa == HGSR_FEAT_MFMA && !has_feat_forms(g->feat_dim)) continue;
       hgsr_opts o = *opts;
       o.tile = t;
       o.schedule = sc;
@@ -1469,7 +1483,7 @@ hgsr_status hgsr_autotune(hgsr_ctx* c, const hgsr_gaussians* g, const float* pos
   (void)hipEventDestroy(b);
   c->tuned_tile = bt;
   c->tuned_sched = bs;
-  c->tuned_feat = bf;
+  keep_feat(bf);
   c->tuned_proj = bp;
   if (result) *result = {bt, bs, bf, best, bp};
   if (cache_path) {

@@ -497,3 +497,39 @@ def test_autotune_choice_and_cache(hg, tmp_path):
     r1b = hg.Renderer()
     res1b = r1b.autotune(scene, _poses(Ps[:1]), K, out1, cache_path=cache)
     assert res1b["proj_group"] == res1["proj_group"] and abs(res1b["ms"] - res1["ms"]) < 1e-4
+
+
+def test_tuning_of_one_width_does_not_choose_for_another(hg):
+    """After tuning on 16 channels (one form) or on 64, an automatic render of
+    32 channels takes the default form, the matrix cores, to the bit."""
+    log("case: feature form per width")
+    sc32, P, cam = synth.tiny_scene(400, 94, width=53, height=45, feat_dim=32, sh_degree=1)
+    want = to_np(_render(hg, sc32, P, cam, feat_accum="mfma")[0]["feat"])
+    assert not np.array_equal(want, to_np(_render(hg, sc32, P, cam, feat_accum="valu")[0]["feat"]))
+    K = hg.Intrinsics.of(cam)
+    for D in (16, 64):
+        sc, _, _ = synth.tiny_scene(400, 95, width=53, height=45, feat_dim=D, sh_degree=1)
+        scene, r = hg.GaussianScene.from_numpy(sc), hg.Renderer()
+        r.autotune(scene, _poses(P), K, r.alloc_outputs(scene, 1, K))
+        got, _ = _render(hg, sc32, P, cam, r=r)
+        assert np.array_equal(to_np(got["feat"]), want), D
+
+
+def test_tuning_cache_of_other_kernels_is_not_used(hg, tmp_path):
+    """A cached line without this build's name, or for another output type, is
+    not taken for its choice."""
+    log("case: cache lines of other kernels")
+    sc, P, cam = synth.tiny_scene(300, 96, width=53, height=45, feat_dim=32)
+    scene, K, r = hg.GaussianScene.from_numpy(sc), hg.Intrinsics.of(cam), hg.Renderer()
+    cache = tmp_path / "tune.jsonl"
+    cache.write_text('{"key": "gfx950/53x45/P1/n300/D32/sh0/sort0/bwd0", "tile": 32, "schedule": 0, '
+                     '"feat_accum": 1, "proj_group": 1, "ms": 9999.0}\n')
+    tune = lambda bf16: hg.Renderer().autotune(scene, _poses(P), K, r.alloc_outputs(scene, 1, K, bf16),  # noqa: E731
+                                               cache_path=str(cache))
+    first = tune(False)
+    assert first["ms"] < 9999.0
+    lines = cache.read_text().splitlines()
+    assert len(lines) == 2
+    tune(True)
+    assert len(cache.read_text().splitlines()) == 3  # the other output type was timed itself
+    assert abs(tune(False)["ms"] - first["ms"]) < 1e-4 and len(cache.read_text().splitlines()) == 3
