@@ -147,7 +147,7 @@ def headline(hg, torch, synth, args):
     log("bench: first render (sizes the workspace)")
     r.render(scene, poses, K, tile=16, sort=args.sort, out=out)
     if args.tile:
-        tile, feat_accum = args.tile, ("valu" if args.feat == "auto" else args.feat)
+        tile, feat_accum = args.tile, ("mfma" if args.feat == "auto" else args.feat)
         opts = r.opts(tile=tile, sort=args.sort, feat_accum=feat_accum)
         tuned = None
     else:
