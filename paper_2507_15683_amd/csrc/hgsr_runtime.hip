@@ -260,7 +260,10 @@ hgsr_status for_each_render_buf(hgsr_ctx* c, int P, const CamArgs& cam, bool lsd
   TRY(f(c->finalT, npix * sizeof(float)));
   TRY(f(c->nused, npix * sizeof(uint32_t)));
   TRY(f(c->part_vis, std::max(P, 1) * sizeof(uint64_t)));
-  TRY(f(c->loss_part, ntile * blend_parts(cam.tile) * sizeof(float)));
+  // a loss share per item of the backward, which a context in the static
+  // scratch has none of: its layout, and so what fits it, is the same at every
+  // split of a tile
+  TRY(f(c->loss_part, ntile * (c->no_alloc ? 1 : blend_parts(cam.tile)) * sizeof(float)));
   if (lsd) {
     TRY(f(c->rec_keys, nrec * sizeof(uint32_t)));
     TRY(f(c->rec_offsets, nrec * sizeof(uint32_t)));

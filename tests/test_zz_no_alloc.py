@@ -131,3 +131,30 @@ def test_overflow_flag_then_clean_call(hg):
     assert st == 0 and flags == 0
     _same(ref, out, "after an overflowing call")
     r.close()
+
+
+def test_larger_tiles_need_less_scratch(hg):
+    """The bytes a render needs, as its refusal states them: 20 per tile (two
+    counters, a range, a loss share) beside what the tile size does not change,
+    up to the scan's block sums (4 bytes per 4096 tiles) and 256-byte rounding
+    of 20 buffers; so what fits the scratch at tile 32 does not depend on how
+    the blend splits a tile."""
+    import re
+    import torch
+    sc, P, _ = synth.terrain_20k_view(0)
+    scene, r = hg.GaussianScene.from_numpy(sc), hg.Renderer()
+    side = 4096
+    K = hg.Intrinsics(3000.0, 3000.0, side / 2, side / 2, side, side)
+    out = dict(rgb=torch.empty(1, device="cuda"), depth=torch.empty(1, device="cuda"),
+               alpha=torch.empty(1, device="cuda"), feat=None)
+    need = {}
+    for tile in (16, 32):
+        log(f"case: refused at tile {tile}")  # nothing is enqueued
+        st, _ = _noalloc(hg, scene, _poses(P), K, r.opts(tile=tile), out, records=1 << 20, keys=1 << 22)
+        assert st == 3
+        need[tile] = int(re.search(r"needs (\d+) bytes", hg._lib.load().hgsr_last_error().decode()).group(1))
+    tiles = {t: (side // t) ** 2 for t in need}
+    diff = need[16] - need[32] - 20 * (tiles[16] - tiles[32])
+    log("beyond 20 bytes per tile:", diff)
+    assert abs(diff) <= 4 * (tiles[16] // 4096) + 20 * 256
+    r.close()
