@@ -260,10 +260,14 @@ hgsr_status for_each_render_buf(hgsr_ctx* c, int P, const CamArgs& cam, bool lsd
   TRY(f(c->finalT, npix * sizeof(float)));
   TRY(f(c->nused, npix * sizeof(uint32_t)));
   TRY(f(c->part_vis, std::max(P, 1) * sizeof(uint64_t)));
-  // a loss share per item of the backward, which a context in the static
-  // scratch has none of: its layout, and so what fits it, is the same at every
-  // split of a tile
-  TRY(f(c->loss_part, ntile * (c->no_alloc ? 1 : blend_parts(cam.tile)) * sizeof(float)));
+  // A loss share per item of the backward: one per tile, four at tile 32.  Sized
+  // for tile 32 too, so that like every buffer here it also holds a larger tile
+  // size than the one it was sized at (a 480x270 view has 510 tiles of 16 and
+  // 540 quadrants of 32), under capture for one.  A context in the static
+  // scratch has no backward: its layout does not depend on the split.
+  const int64_t quadrants = blend_parts(32) * static_cast<int64_t>((cam.W + 31) / 32) * ((cam.H + 31) / 32);
+  const int64_t shares = c->no_alloc ? ntile : P * std::max<int64_t>(cam.tiles_per_pose, quadrants);
+  TRY(f(c->loss_part, shares * sizeof(float)));
   if (lsd) {
     TRY(f(c->rec_keys, nrec * sizeof(uint32_t)));
     TRY(f(c->rec_offsets, nrec * sizeof(uint32_t)));

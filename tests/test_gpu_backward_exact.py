@@ -1,7 +1,8 @@
 """GPU backward against a dense 64-bit evaluation with autograd on the CPU
 (every pixel against every Gaussian, no tiles and no lists), over lists of
 several staging rounds; the summation error of the mean gradient; infinite
-features and output gradients; one shared target over several pose blocks."""
+features and output gradients; one shared target over several pose blocks; a
+captured step at another tile size than the workspace was sized at."""
 import math
 
 import numpy as np
@@ -243,3 +244,37 @@ def test_shared_target_over_several_pose_blocks(hg):
     assert np.array_equal(la, to_np(lb))
     for k in range(11):
         assert _rel(to_np(gb["pose"])[k], pa[k]) < 1e-6, k
+
+
+def test_captured_step_at_a_larger_tile_than_sized(hg):
+    """A workspace sized by an eager step at tile 16 holds a captured one at
+    tile 32, where an odd size has more quadrants than it had tiles of 16 (540
+    against 510); every replay gives the eager step's loss and pose gradient."""
+    import torch
+    sc, P, cam = synth.tiny_scene(600, 160, width=480, height=270, feat_dim=8, sh_degree=0)
+    scene, K = hg.GaussianScene.from_numpy(sc), hg.Intrinsics.of(cam)
+    log("case: captured step at tile 32 after an eager one at tile 16")
+    tgt = hg.Renderer().render(scene, _t(synth.perturb_poses(P[0], 1, 161, 1.0, 2.0)), K)
+    poses, opts = _t(P), hg.Renderer().opts(tile=32)
+    e = hg.Renderer()
+    e.render(scene, poses, K, tile=32)
+    loss, g = e.residual_backward(tgt["rgb"], tgt["feat"])
+    want = to_np(loss).copy(), to_np(g["pose"]).copy()
+    r, s = hg.Renderer(), torch.cuda.Stream()
+    out = r.render(scene, poses, K, tile=16)
+    loss, g = r.residual_backward(tgt["rgb"], tgt["feat"])
+    torch.cuda.synchronize()
+    with torch.cuda.stream(s):
+        r.graph_begin(s)
+        try:
+            r.render_into(scene, poses, K, out, opts, s)
+            r.residual_backward(tgt["rgb"], tgt["feat"], loss=loss, grads=g, stream=s)
+        finally:
+            r.graph_end()
+        for _ in range(3):
+            loss.zero_()
+            g["pose"].zero_()
+            r.graph_launch(1, s)
+            s.synchronize()
+            assert np.array_equal(to_np(loss), want[0])
+            assert _rel(to_np(g["pose"]), want[1]) < 1e-6
