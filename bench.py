@@ -804,7 +804,7 @@ def main():
     ap.add_argument("--tile", type=int, default=0, help="0: autotuned")
     ap.add_argument("--sort", default="bucket")
     ap.add_argument("--feat", choices=["auto", "valu", "mfma"], default="auto",
-                    help="feature accumulation with a fixed --tile (auto: the VALU)")
+                    help="feature accumulation with a fixed --tile (auto: the library's default)")
     ap.add_argument("--layout", choices=["spatial", "given"], default="spatial",
                     help="scene storage order: spatial (Morton, the library's layout) or as generated")
     ap.add_argument("--no-fwd-bwd", action="store_true")

@@ -35,7 +35,7 @@ constexpr int kBwdGcRow = 8;    // words per row of 8 pixel gradients
 // block (16 tiles: 0.6 MB at 32 channels) is then fetched once per block of
 // poses into the XCD's L2, whose poses still pass over neighbouring tiles
 // close together (records and half lines of the maps).  64 poses at 960x540:
-// 3,323 -> 3,258 us, 16 at 480x270: 266 -> 251 us; all poses per run 3-5 %
+// 3,285 -> 3,230 us, 16 at 480x270: 254 -> 249 us; all poses per run 3-5 %
 // slower than pose after pose, runs of 60 tiles no faster.
 constexpr int kPoseBlock = 8;
 constexpr int kTileRun = 16;
@@ -110,19 +110,21 @@ __device__ __forceinline__ bool finite_bits(float v) { return (__float_as_uint(v
 
 // The reverse replay of one (pose, tile) or tile quadrant.
 //
-// Bound by the VALU (about 2,500 instructions per wave of 35 splats, 70 % busy)
-// beside the feature maps' traffic.  A splat's gradient sums over a wave's 64
-// pixels are not reduced across lanes splat by splat: each lane writes two
-// numbers per splat to LDS, dL/dpower d and the blend weight w, and after eight
-// splats the wave reads them back transposed -- a lane takes one splat's row of
-// eight pixels -- and forms the sums of d, d dx, d dx^2 and w g there, every
-// lane busy, with one cross-lane step per eight splats.  With the conic
-// (a, b, c) the sums kept per record are d (a dx + b dy) and d (b dx + c dy),
+// Bound by the VALU (2,630 instructions per wave at 64 poses of 960x540, three
+// quarters of the issue slots at 2.4 GHz) beside the feature maps' traffic.  A
+// splat's gradient sums over a wave's 64 pixels are not reduced across lanes
+// splat by splat: each lane writes two numbers per splat to LDS, dL/dpower d
+// and the blend weight w, and after eight splats the wave reads them back
+// transposed -- a lane takes one splat's row of eight pixels -- and forms the
+// sums there, every lane busy, with one cross-lane step per eight splats.  With
+// the conic (a, b, c) those kept per record are d (a dx + b dy), d (b dx + c dy),
 // the mean's gradient, the moments d dx^2, d dx dy, d dy^2, d, and w gZ, w gC;
 // the projection backward turns the moments into conic and opacity gradients.
 // The mean's two sums are formed per pixel: along a needle a dx and b dy cancel
 // there, and sums of d dx and d dy combined at the end miss the 64-bit value by
-// up to 48 x 2^-24 of the terms (needles of 60 px), these by less than 0.1.  The waves keep their sums apart in LDS until the flush: float
+// up to 48 x 2^-24 of the terms (needles of 60 px), these by less than 0.1, for
+// four more instructions per splat (no features, tile 16, 8 poses of 480x270:
+// 181 -> 194 us).  The waves keep their sums apart in LDS until the flush: float
 // atomics there take about a cycle per lane (300 of 3,700 us at 64 poses).
 //
 // The feature part of h_j = gF . f_j is, for 16 splats and 64 pixels, a matrix
@@ -143,9 +145,12 @@ __device__ __forceinline__ bool finite_bits(float v) { return (__float_as_uint(v
 // and added it to memory from one lane.
 //
 // Before and after, blend backward alone: 64 poses at 960x540, 32 channels,
-// pose only: 3,744 -> 3,260 us; 16 poses at 480x270: 291 -> 251 us; one pose
-// at 480x270: 98 -> 63 us; one 640x480 view with all Gaussian gradients: 711 ->
-// 133 us.  Five waves per SIMD (96 registers) spill: 5,040 us at 64 poses.
+// pose only: 3,810 -> 3,230 us; 16 poses at 480x270: 290 -> 249 us; one pose
+// at 480x270: 98 -> 64 us; one 640x480 view with all Gaussian gradients: 710 ->
+// 138 us.  Pose only, up to 32 channels, tile 16 and 32: held to four waves per
+// SIMD, which takes all 128 registers and spills none (12 spilled, the staged
+// record among them: 230 us instead of 222 at one 1920x1080 pose); five waves
+// (96 registers) spill: 5,040 us at 64 poses.
 //
 // Non-finite output gradients reach only the splats blended at their pixels:
 // a wave that holds any (`bad`) leaves zero weights out of its sums.
@@ -253,8 +258,9 @@ __device__ __forceinline__ void blend_bwd_item(const BackArgs& a, const int item
   };
   auto stage_load = [&](uint2 range, uint32_t b0, uint32_t gid) {
     if (range.x + b0 + st_e < range.y) {
+      // keeps the two 64-bit addresses inside the round, out of the walk's registers
       int sub = st_sub;
-      asm volatile("" : "+v"(sub));  // keeps the two 64-bit addresses inside the round instead of in registers for the walk
+      asm volatile("" : "+v"(sub));
       const floatx4* sp = reinterpret_cast<const floatx4*>(a.recs + (st_lv & kRecMask));
       if (sub < 3) st_rec0 = sp[sub];
       if (RV > 1 && sub + SHARE < 3) st_rec1 = sp[sub + SHARE];
@@ -280,7 +286,8 @@ __device__ __forceinline__ void blend_bwd_item(const BackArgs& a, const int item
       if (RV > 1 && st_sub + SHARE < 3) sp[st_sub + SHARE] = st_rec1;
       if (RV > 2) sp[2] = st_rec2;
       if constexpr (!AHEAD) {  // a thread stages a whole splat: its record holds the Gaussian's index
-        const uint4* fv = reinterpret_cast<const uint4*>(a.feat) + static_cast<int64_t>(__float_as_uint(st_rec1[3])) * DV;
+        const int64_t gid = __float_as_uint(st_rec1[3]);
+        const uint4* fv = reinterpret_cast<const uint4*>(a.feat) + gid * DV;
 #pragma unroll
         for (int q = 0; q < DV; ++q) {
           const uint4 f = fv[q];

@@ -13,13 +13,14 @@
 // take its transmittance below 1e-4; the round loop ends when every pixel of
 // the block has stopped.  Outputs are planar per pose.
 //
-// What bounds it: with 32 channels, at 64 poses of 752x480 over a million
-// Gaussians, 1.66 ms of walking (vector instructions)
-// and 0.7 ms in which the 4.9 GB of planes leave at the rate of HBM;
-// 2.50 -> 2.35 ms, one 1920x1080 pose 142 -> 102 us, one 752x480 pose
-// 67 -> 42 us against batches of 128 with the feature FMAs on the VALU.  A
-// fifth wave per SIMD spills (3.2 ms); planes written through LDS as 64-byte
-// rows cost more in LDS and barriers (+0.27 ms) than they give.
+// What bounds it: with 32 channels, at 64 poses of 960x540 over a million
+// Gaussians, the walk's vector instructions (1,700 per wave); the launch takes
+// 1.61 ms without a feature buffer, and the stores of its 4.2 GB of feature
+// planes add 0.74 ms to that, part of them under the walk.  2.50 -> 2.35 ms, one
+// 1920x1080 pose 137 -> 103 us, one 480x270 pose 67 -> 42 us against batches of
+// 128 with the feature FMAs on the VALU.  A fifth wave per SIMD spills (3.2 ms);
+// planes written through LDS as 64-byte rows cost more in LDS and barriers
+// (+0.27 ms) than they give.
 #include "hgsr_device.hpp"
 #include "launch.hpp"
 
@@ -47,7 +48,11 @@ constexpr int kFeatRound = 4;  // 16-byte feature reads per round of the FMA for
 // (top, middle and last 8 significant bits), so the products are exact and only
 // the order of the FP32 sum differs from one FMA per splat and channel.  The
 // FMA form spends 32 of 70 VALU instructions and 8 of 11 LDS reads per splat
-// on the features (both units near their limits); this one about 7 and 1.
+// on the features (both units near their limits); this one about 7 and 1.  It
+// takes 0.67 to 0.89 of the FMA form's time with 32 channels and 0.47 to 0.85
+// with 64 over the tile sizes and views measured (64 channels, tile 16, 8 poses
+// of 480x270: 431 -> 224 us; one of 1920x1080: 286 -> 225 us), though with 64 it
+// takes 168 registers against 140.
 // A piece of eight channels that holds a non-finite value enters the product as
 // zeros and is summed apart, at the pixels that blend its splat (a zero weight
 // times infinity would reach the others).
