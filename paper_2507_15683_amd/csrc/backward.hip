@@ -110,8 +110,8 @@ __device__ __forceinline__ bool finite_bits(float v) { return (__float_as_uint(v
 
 // The reverse replay of one (pose, tile) or tile quadrant.
 //
-// Bound by the VALU (2,630 instructions per wave at 64 poses of 960x540, three
-// quarters of the issue slots at 2.4 GHz) beside the feature maps' traffic.  A
+// Bound by the VALU (2,630 instructions per wave at 64 poses of 960x540, waves
+// waiting 38 % of their cycles) beside the feature maps' traffic.  A
 // splat's gradient sums over a wave's 64 pixels are not reduced across lanes
 // splat by splat: each lane writes two numbers per splat to LDS, dL/dpower d
 // and the blend weight w, and after eight splats the wave reads them back
