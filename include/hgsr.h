@@ -667,12 +667,12 @@ hgsr_status hgsr_debug_tile_lists(hgsr_ctx* ctx, int32_t pose, uint32_t* ranges,
  * the context's default (opts->tile == 0, opts->schedule == HGSR_SCHED_AUTO,
  * opts->feat_accum == HGSR_FEAT_AUTO) and append it to the JSON-lines cache
  * file `cache_path` (host string, may be NULL), which later calls on the same
- * shape and output type by the same build of the library read instead of
- * timing.  The feature accumulation is kept per width (32 and 64 channels; the
- * others have one form).  with_backward != 0 times each render
- * followed by the pose backward (dL/drgb and, for FP32 feature maps,
- * dL/dfeat taken as the rendered maps themselves), the cost of a refinement
- * step, instead of the render alone.  Synchronises `stream`. */
+ * shape and output type with the same kernels read instead of timing.  The
+ * feature accumulation is kept per width (32 and 64 channels; the others have
+ * one form).  with_backward != 0 times each render followed by the pose backward
+ * (dL/drgb and, for FP32 feature maps, dL/dfeat taken as the rendered maps
+ * themselves), the cost of a refinement step, instead of the render alone.
+ * Synchronises `stream`. */
 hgsr_status hgsr_autotune(hgsr_ctx* ctx, const hgsr_gaussians* g, const float* poses, int32_t P,
                           const hgsr_intrinsics* K, const hgsr_opts* opts, const hgsr_outputs* out,
                           int32_t with_backward, const char* cache_path, hgsr_tune_result* result,

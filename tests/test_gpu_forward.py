@@ -516,8 +516,8 @@ def test_tuning_of_one_width_does_not_choose_for_another(hg):
 
 
 def test_tuning_cache_of_other_kernels_is_not_used(hg, tmp_path):
-    """A cached line without this build's name, or for another output type, is
-    not taken for its choice."""
+    """A cached line that does not name the present kernels, or for another
+    output type, is not taken for its choice."""
     log("case: cache lines of other kernels")
     sc, P, cam = synth.tiny_scene(300, 96, width=53, height=45, feat_dim=32)
     scene, K, r = hg.GaussianScene.from_numpy(sc), hg.Intrinsics.of(cam), hg.Renderer()
